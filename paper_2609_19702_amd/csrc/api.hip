@@ -132,28 +132,51 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d) {
   C = std::max<int64_t>(block_rows, (C + block_rows - 1) / block_rows * block_rows);
   S = std::max<int64_t>(1, (rows_max + C - 1) / C);
   if (pairs * S > (int64_t(1) << 31) - 1) return DSA_ERR_INVALID_ARG;
+  // What callers allocate: sized for these splits, also where one workgroup
+  // per pair (below) needs none of it.
+  d->ws_bytes = S > 1 ? static_cast<size_t>(pairs) * S * G * (d->D + 2) * sizeof(float) : 0;
+  // Tiles of rows [r0, r1): they stop at the prompt/decode boundary, so a
+  // split can have one more than C / tile.
+  auto tiles_of = [&](int64_t r0, int64_t r1, int64_t tile_rows) {
+    const int64_t pe = std::min<int64_t>(r1, d->Lp);
+    const int64_t wst = std::max<int64_t>(r0, d->Lp);
+    return (pe > r0 ? (pe - r0 + tile_rows - 1) / tile_rows : 0) +
+           (r1 > wst ? (r1 - wst + tile_rows - 1) / tile_rows : 0);
+  };
+  // One workgroup per pair (kOnePairs, internal.h).  Launches of more than
+  // kKeptReadPairs pairs that keep lists stay split: one workgroup is faster
+  // there too (70 pairs of 138 rows, d = 64: 10.1 -> 7.1 us), but their splits
+  // and the combine that stores the lists are what the kept-list tests run.
+  const bool one = pairs <= kOnePairs && rows_max <= max_fused_split(d->MF) &&
+                   !(d->kept_read && pairs > kKeptReadPairs) &&
+                   !d->MF && sparse && G == 1;
+  d->wide = one && !d->MF;
+  if (one) {
+    S = 1;
+    C = std::max<int64_t>(64, (rows_max + 63) / 64 * 64);
+  }
   d->C = static_cast<int>(C);
   d->S = static_cast<int>(S);
-  // Waves per workgroup: the most tiles any split has (tiles stop at the
-  // prompt/decode boundary, so a split can have one more than C / tile).
-  // fp8 caches load twice the elements per lane, so the vector-ALU tile
-  // holds twice the rows (at most 64) and a split has fewer tiles.
+  // Waves per workgroup: at most the most tiles any split has.  fp8 caches
+  // load twice the elements per lane, so the vector-ALU tile holds twice the
+  // rows (at most 64) and a split has fewer tiles.
   auto waves_for = [&](int64_t tile_rows) {
     int64_t max_tiles = 1;
-    for (int64_t sp = 0; sp < S; ++sp) {
-      const int64_t r0 = sp * C, r1 = std::min(rows_max, r0 + C);
-      const int64_t pe = std::min<int64_t>(r1, d->Lp);
-      const int64_t wst = std::max<int64_t>(r0, d->Lp);
-      const int64_t tiles = (pe > r0 ? (pe - r0 + tile_rows - 1) / tile_rows : 0) +
-                            (r1 > wst ? (r1 - wst + tile_rows - 1) / tile_rows : 0);
-      max_tiles = std::max(max_tiles, tiles);
-    }
-    const int cap = d->MF ? (sparse ? kWavesMfma : kWavesMfmaDense) : kWavesValu;
+    for (int64_t sp = 0; sp < S; ++sp)
+      max_tiles = std::max(max_tiles, tiles_of(sp * C, std::min(rows_max, sp * C + C), tile_rows));
+    const int cap = d->wide ? kWavesWide
+                    : !d->MF ? kWavesValu
+                    : sparse ? kWavesMfma
+                             : kWavesMfmaDense;
     return static_cast<int>(std::min<int64_t>(cap, max_tiles));
   };
-  d->NW = waves_for(block_rows);
-  d->NW_fp8 = waves_for(d->MF ? kMfmaTile : 2 * rows_per_instr * unroll_for(G, d->D, 1));
-  d->ws_bytes = S > 1 ? static_cast<size_t>(pairs) * S * G * (d->D + 2) * sizeof(float) : 0;
+  if (d->wide) {
+    d->NW = waves_for(rows_per_instr * unroll_wide(d->D, 2));
+    d->NW_fp8 = waves_for(2 * rows_per_instr * unroll_wide(d->D, 1));
+  } else {
+    d->NW = waves_for(block_rows);
+    d->NW_fp8 = waves_for(d->MF ? kMfmaTile : 2 * rows_per_instr * unroll_for(G, d->D, 1));
+  }
   return DSA_OK;
 }
 

@@ -533,12 +533,13 @@ __host__ __device__ constexpr uint32_t mf_lds_bytes(int nw) {
   return mf_vt_bytes<D>(nw) + ((red + 15u) & ~15u);
 }
 
-template <class KV, int D, int G, int U, bool FUSED, bool KL, bool MF>
+template <class KV, int D, int G, int U, bool FUSED, bool KL, bool MF, int NWM>
 __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   constexpr int EPL = KV::kEpl;    // elements a lane loads per 16-byte access
   constexpr int LPR = D / EPL;     // lanes per row (V layout; K layout too without MF)
   constexpr int RPI = 64 / LPR;    // rows per load instruction
-  constexpr int UU = MF ? U : unroll_for(G, D, KV::kBytes);  // loads in flight per operand
+  constexpr int UU = MF ? U : cap_unroll(U, D, KV::kBytes);  // loads in flight per operand
+  constexpr bool WIDE = !MF && NWM > kWaves;  // decode_wide_kernel
   constexpr int T = MF ? kMfmaTile : RPI * UU;      // rows per wave tile (<= 64)
   constexpr int NK = D / 32;       // MFMA k-steps per 16 rows (MF only)
   constexpr int KPL = EPL / 8;     // MFMA k-steps per K load (MF only)
@@ -549,7 +550,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   // The MFMA tile keeps them in its dynamic LDS block (sized for the
   // launch's waves, mf_lds_bytes), after the per-wave V tiles.  The fused
   // step's skip bitmaps (one per wave) follow in dynamic LDS.
-  constexpr int kRedBytes = MF ? 16 : kWaves * G * (D + 2) * 4;
+  constexpr int kRedBytes = MF ? 16 : NWM * G * (D + 2) * 4;
   __shared__ __attribute__((aligned(16))) unsigned char smem[kRedBytes];
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_lds[];
   const int nw_launch = blockDim.x >> 6;
@@ -835,7 +836,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     // barrier: the loop preheader of the ranking waits for the stored
     // offsets with a vmcnt that, after the conditional hoisted loads, must
     // count all of them.  Issuing its V loads earlier measured slower.)
-    if constexpr (!MF) {
+    if constexpr (!MF && !WIDE) {
       if (Wn > 0 && P > 0) __syncthreads();
     }
   }
@@ -1061,7 +1062,6 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   // issued before the first is used, with no branches: slots past the
   // workgroup's waves read its last wave again (the maximum does not
   // change) and add nothing (the waves are added in order).
-  constexpr int NWM = MF ? kWavesMfma : kWaves;  // waves of a workgroup at most
   for (int g = wave; g < G; g += nwaves) {
     float mw[NWM], lw[NWM], a0[NWM], a1[NWM];
 #pragma unroll
@@ -1136,7 +1136,21 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
 template <class KV, int D, int G, int U, bool FUSED, bool KL>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G == 1 ? 4 : 1, 8)))
 void decode_kernel(DecodeArgs a) {
-  decode_body<KV, D, G, U, FUSED, KL, false>(a);
+  decode_body<KV, D, G, U, FUSED, KL, false, kWaves>(a);
+}
+
+// One query head per KV head, at most one (request, KV head) pair per CU: one
+// workgroup of up to kWavesWide waves per pair, a tile or two per wave.  Bound
+// by latency (the launch and four dependent memory round trips), so the tiles
+// are smaller than the throughput kernel's (16 rows of d = 128 in bf16, 40
+// otherwise: 7.1 us per Janus-like layer at batch 1 against 7.7 us with 32
+// rows and 8.1 us with 8), no barrier holds the prompt rows' V loads behind
+// the ranking, and nothing is left for a combine kernel (8.5 us per layer with
+// five splits per pair and the combine; LlamaGen-XL-like 8.1 -> 5.5 us).
+template <class KV, int D, bool FUSED, bool KL>
+__global__ __launch_bounds__(64 * kWavesWide) __attribute__((amdgpu_waves_per_eu(4, 8)))
+void decode_wide_kernel(DecodeArgs a) {
+  decode_body<KV, D, 1, unroll_wide(D, KV::kBytes), FUSED, KL, false, kWavesWide>(a);
 }
 
 // The grouped-head (MFMA) tile holds K and V of two 32-row tiles and the
@@ -1144,7 +1158,7 @@ void decode_kernel(DecodeArgs a) {
 template <class KV, int D, int G, bool FUSED, bool KL>
 __global__ __launch_bounds__(64 * kWavesMfma) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void decode_mfma_kernel(DecodeArgs a) {
-  decode_body<KV, D, G, 2, FUSED, KL, true>(a);
+  decode_body<KV, D, G, 2, FUSED, KL, true, kWavesMfma>(a);
 }
 
 // out = sum_s e^{m_s - M} acc_s / sum_s e^{m_s - M} l_s over the splits of
@@ -1272,6 +1286,12 @@ void launch_split(const Derived& d, const DecodeArgs& a, hipStream_t st, hipEven
                             st, t0, t1, 0, a);
     else
       decode_mfma_kernel<KV, D, G, FUSED, KL><<<grid, block, lds, st>>>(a);
+  } else if (G == 1 && d.wide) {
+    if (t0 || t1)
+      hipExtLaunchKernelGGL(decode_wide_kernel<KV, D, FUSED, KL>, dim3(grid), dim3(block), lds,
+                            st, t0, t1, 0, a);
+    else
+      decode_wide_kernel<KV, D, FUSED, KL><<<grid, block, lds, st>>>(a);
   } else {
     if (t0 || t1)
       hipExtLaunchKernelGGL(decode_kernel<KV, D, G, U, FUSED, KL>, dim3(grid), dim3(block), lds,

@@ -28,6 +28,7 @@ struct Derived {
   int S;          // splits per (request, KV head), upper bound
   int NW;         // waves per decode workgroup (1..kWaves), bf16 caches
   int NW_fp8;     // the same for fp8 caches (tiles of twice the rows)
+  bool wide;      // one workgroup of up to kWavesWide waves per (request, KV head)
   bool MF;        // grouped query heads on the MFMA tile (uses_mfma_tile(G))
   int kept_read;  // 1: selections store kept lists and the fused step reads its kept rows from them
   size_t ws_bytes;
@@ -96,6 +97,7 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d);
 
 constexpr int kWaves = 4;          // waves per workgroup (the MFMA decode tile: kWavesMfma)
 constexpr int kBlock = 64 * kWaves;
+constexpr int kWavesWide = 16;     // most waves of a decode_wide_kernel workgroup (128 registers)
 constexpr int kWavesMfma = DSA_TUNE_MFMA_WAVES;
 constexpr int kWavesValu = DSA_TUNE_VALU_WAVES;
 constexpr int kWavesMfmaDense = DSA_TUNE_MFMA_WAVES_DENSE;
@@ -118,6 +120,12 @@ constexpr int kKeptReadCap = DSA_TUNE_KEPT_READ_CAP;
 // ahead of the position): in launches of few pairs, and in the others.
 constexpr int kKeptReadMax = 512;
 constexpr int kKeptReadMaxWide = 256;
+// One workgroup per (request, KV head), and no combine, in launches of at most
+// one pair per CU: the launch is bound by latency, and the second kernel costs
+// 3.3 us of it.  Vector-ALU tile,
+// sparse modes (32 to 256 pairs: 15-30% less per layer; at 512 pairs the
+// four-wave workgroups of the general kernel are 4% faster).
+constexpr int kOnePairs = 256;
 static_assert(kMaxFusedSplit % 64 == 0 && kMaxFusedSplit <= 1024, "fused split rows");
 static_assert(kMaxFusedSplitMfma % 64 == 0 && kMaxFusedSplitMfma <= 1024, "fused split rows");
 // Rows of one sparse-mode split at most, by tile.
@@ -135,12 +143,18 @@ constexpr int unroll_of(int G) {
 // holds at most 64 rows (one kept position per lane), and fp8 caches may be
 // capped lower.  A lane loads 16 bytes, so one instruction covers
 // 1024 / (d * elem_bytes) rows.
-constexpr int unroll_for(int G, int d, int elem_bytes) {
+constexpr int cap_unroll(int u, int d, int elem_bytes) {
   const int rpi = 1024 / (d * elem_bytes);
-  int u = unroll_of(G);
   if (rpi * u > 64) u = 64 / rpi;
   if (elem_bytes == 1 && u > DSA_TUNE_UNROLL_FP8) u = DSA_TUNE_UNROLL_FP8;
   return u;
+}
+constexpr int unroll_for(int G, int d, int elem_bytes) {
+  return cap_unroll(unroll_of(G), d, elem_bytes);
+}
+// The same on the wide kernel (decode_wide_kernel).
+constexpr int unroll_wide(int d, int elem_bytes) {
+  return cap_unroll(d == 128 && elem_bytes == 2 ? 4 : 5, d, elem_bytes);
 }
 constexpr int kMaxFusedWindow = 16384;  // N_r of the fused step (skip bitmap per wave in LDS)
 constexpr float kNegBig = -1.0e30f;  // "no score yet": finite, so exp2 of a difference is 0

@@ -1,0 +1,69 @@
+"""The launch rules at their edges, each step (fused and as three calls)
+against the oracle: one workgroup per (request, KV head) with as many waves
+as it has tiles."""
+
+import random
+
+import pytest
+import torch
+
+from paper_2609_19702_amd import binding as B
+from paper_2609_19702_amd import synth
+from tests.gpu_util import (DEV, c_replay_states, check_layer_vs_oracle, fp8_request_arrays,
+                            request_arrays, say, states_to_buffer)
+from tests.test_gpu_mfma_tiles import positions, run
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # name, B, Hq, Hkv, d, L_p, grid, N_r, N_att, sinks, splits > 1, waves
+    # one query head per KV head: 16-row tiles at d = 128, 40-row ones at d = 64
+    ("wide_no_prompt", 12, 2, 2, 128, 0, 8, 20, 6, 0, False, 1),
+    ("wide_16_tiles", 12, 3, 3, 128, 225, 12, 60, 16, 0, False, 16),
+    ("wide_18_tiles", 12, 4, 4, 128, 256, 24, 256, 29, 4, False, 16),
+    ("wide_512_rows", 12, 2, 2, 128, 103, 40, 600, 409, 0, False, 16),
+    ("wide_513_rows", 12, 2, 2, 128, 104, 40, 600, 409, 0, True, 3),
+    ("wide_d64", 12, 5, 5, 64, 121, 20, 130, 41, 4, False, 6),
+    ("wide_256_pairs", 16, 16, 16, 64, 41, 12, 60, 9, 0, False, 3),
+    ("pairs_257", 257, 1, 1, 64, 41, 12, 60, 9, 0, False, 2),
+]
+
+
+@pytest.mark.parametrize("kv_type", ["bf16", "fp8"])
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_launch_rule_edges_match_oracle(case, kv_type):
+    name, Bn, Hq, Hkv, d, Lp, grid, N_r, N_att, sinks, split, waves = case
+    L = grid * grid
+    p = B.make_params(Lp, grid, grid, N_r, N_att, B.MODE_DIAGONAL, sinks)
+    s = B.make_shape(Bn, Hq, Hkv, d)
+    info = B.launch_info(p, s)
+    say("launch rule", name, kv_type, "splits", info.max_splits, "waves", info.waves_per_group)
+    assert (info.max_splits > 1) == split and info.waves_per_group == waves
+    ts = positions(Bn, L, N_r, N_att, seed=Bn + d)
+    rng = random.Random(N_att * 13 + Hkv)
+    w = synth.Workload(name, 1, Bn, Hq, Hkv, d, Lp, grid, grid, N_r, outlier_frac=0.01)
+    kv = synth.layer_kv(w, 0, DEV)
+    arrays_of = lambda b: request_arrays(kv, b, Lp)  # noqa: E731
+    if kv_type == "fp8":
+        kv = synth.to_fp8(kv)
+        arrays_of = lambda b: fp8_request_arrays(kv, b, Lp, Hkv)  # noqa: E731
+    q = synth.layer_query(w, 0, DEV)
+    # the oracle's states count steps from the first position after the sinks
+    states, _ = c_replay_states(N_r, N_att - sinks, L, [t - sinks for t in ts], Hkv, rng)
+    st0 = states_to_buffer(p, s, states, ts)
+    pos = torch.tensor(ts, dtype=torch.int32, device=DEV)
+    lay = B.kv_layout(kv.k, k_scale=kv.k_scale, v_scale=kv.v_scale)
+    arrays = [arrays_of(b) for b in range(Bn)]
+    got = []
+    for fused in (True, False):
+        bufs, st = run(p, s, q, kv, pos, st0, fused, lay)
+        forced = check_layer_vs_oracle(p, s, q, arrays, ts, states, bufs.plan, bufs.out, st,
+                                       bufs.logits if kv_type == "bf16" else None)
+        assert forced <= 2
+        got.append((bufs, st))
+    (fb, fst), (sb, sst) = got
+    assert torch.equal(fb.out, sb.out) and torch.equal(fst, sst)
+    assert torch.equal(fb.logits, sb.logits)
+    cnt, flg, idx = B.plan_views(p, s, fb.plan)
+    rcnt, rflg, ridx = B.plan_views(p, s, sb.plan)
+    assert torch.equal(cnt, rcnt) and torch.equal(flg, rflg) and torch.equal(idx, ridx)
