@@ -147,13 +147,18 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d) {
   // kKeptReadPairs pairs that keep lists stay split: one workgroup is faster
   // there too (70 pairs of 138 rows, d = 64: 10.1 -> 7.1 us), but their splits
   // and the combine that stores the lists are what the kept-list tests run.
-  const bool one = pairs <= kOnePairs && rows_max <= max_fused_split(d->MF) &&
+  // Where N_att covers the whole image the rows are cut as in dense mode.
+  const bool one = sparse && p->n_att < ldec && pairs <= kOnePairs &&
+                   rows_max <= max_fused_split(d->MF) &&
                    !(d->kept_read && pairs > kKeptReadPairs) &&
-                   !d->MF && sparse && G == 1;
+                   (d->MF ? tiles_of(0, rows_max, kMfmaTile) <= kOneTilesMfma ||
+                                pairs >= kOnePairsMfma
+                          : G == 1);
   d->wide = one && !d->MF;
   if (one) {
+    const int64_t unit = d->MF ? kMfmaTile : 64;
     S = 1;
-    C = std::max<int64_t>(64, (rows_max + 63) / 64 * 64);
+    C = std::max<int64_t>(unit, (rows_max + unit - 1) / unit * unit);
   }
   d->C = static_cast<int>(C);
   d->S = static_cast<int>(S);
@@ -166,7 +171,7 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d) {
       max_tiles = std::max(max_tiles, tiles_of(sp * C, std::min(rows_max, sp * C + C), tile_rows));
     const int cap = d->wide ? kWavesWide
                     : !d->MF ? kWavesValu
-                    : sparse ? kWavesMfma
+                    : sparse ? waves_mfma(pairs * S)
                              : kWavesMfmaDense;
     return static_cast<int>(std::min<int64_t>(cap, max_tiles));
   };
@@ -410,6 +415,7 @@ static dsa_status decode_impl(const dsa_params* p, const dsa_shape* s, const voi
   a.plan_cap = d.plan_cap;
   a.C = d.C;
   a.S = d.S;
+  a.wl_rows = std::min(d.C, (d.plan_cap + 3) & ~3);  // C is a multiple of the tile
   // No ring (0), or a ring of at least L_dec slots, maps every position to
   // itself; otherwise a.ring >= N_r > 0 slots rotate after the sinks.
   a.ring = (kv->ring_rows == 0 || kv->ring_rows >= d.Ldec)

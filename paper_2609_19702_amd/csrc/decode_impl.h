@@ -430,7 +430,7 @@ __device__ __forceinline__ void mf_compute(const DecodeArgs& a, int lane, int rs
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int r = rs + 16 * h + 4 * lq + j;
-        if (r < re) wls[lr * kMaxFusedSplitMfma + (r - a.Lp - w0)] = sc[h][j] * sl;
+        if (r < re) wls[(r - a.Lp - w0) * G + lr] = sc[h][j] * sl;
       }
   }
   // V rows of the tile into the wave's LDS tile, as bf16 (exact for fp8).
@@ -513,10 +513,10 @@ __device__ __forceinline__ void mf_compute(const DecodeArgs& a, int lane, int rs
   fence_wave();  // the next tile rewrites the V tile
 }
 
-// Dynamic LDS of the window logits of a sparse-mode split: G heads of at
-// most max_fused_split rows (a multiple of 16 bytes).
-__host__ __device__ constexpr uint32_t wl_lds_bytes(int G, bool mf) {
-  return static_cast<uint32_t>(G) * max_fused_split(mf) * 4u;
+// Dynamic LDS of the window logits of a sparse-mode split, G heads of `rows`
+// window rows (a multiple of 4 rows, so of 16 bytes).
+__host__ __device__ constexpr uint32_t wl_lds_bytes(int G, int rows) {
+  return static_cast<uint32_t>(G) * rows * 4u;
 }
 
 // Dynamic LDS of an MFMA-tile workgroup of nw waves: the V tiles, then the
@@ -560,10 +560,13 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   __shared__ int kp_s[FUSED ? KS : 1];  // fused: kept positions of the split
   // MF: one V tile per wave (bf16, rows padded), read back transposed
   uint16_t* vt_w = reinterpret_cast<uint16_t*>(dyn_lds) + (threadIdx.x >> 6) * kMfmaTile * (D + kVPad);
-  // Sparse mode: the split's window logits, head g at wl_s[g * KS + rank]
-  // (dynamic LDS; none in dense mode).
+  // Sparse mode: the split's window logits, head g of window row i at
+  // wl_s[i * G + g] (dynamic LDS; none in dense mode).  The MFMA tile, whose
+  // workgroups share a CU only if their LDS fits, holds as many rows as a
+  // split can have; the vector-ALU tile always KS.
   float* wl_s = reinterpret_cast<float*>(dyn_lds + mf_bytes);
-  const uint32_t wl_bytes = a.mode != DSA_MODE_DENSE ? wl_lds_bytes(G, MF) : 0u;
+  const uint32_t wl_bytes =
+      a.mode != DSA_MODE_DENSE ? wl_lds_bytes(G, MF ? a.wl_rows : KS) : 0u;
   uint32_t* bm_all = reinterpret_cast<uint32_t*>(dyn_lds + mf_bytes + wl_bytes);
 
   const int lane = threadIdx.x & 63;
@@ -903,7 +906,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
         const int r = rs + u * RPI + rg;
         if (r < re) {
 #pragma unroll
-          for (int g = 0; g < G; ++g) wl_s[g * KS + (r - a.Lp - w0)] = sc[u][g] * sl;
+          for (int g = 0; g < G; ++g) wl_s[(r - a.Lp - w0) * G + g] = sc[u][g] * sl;
         }
       }
     }
@@ -1026,7 +1029,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   bool sel = false;
   const int ksel = rr.t - (a.Natt - 1);
   const int nwin = n - a.Lp - a.Ns;
-  float* const wl_win = wl_s + a.Ns;  // head g's window logits at wl_win[g * KS + j]
+  float* const wl_win = wl_s + a.Ns * G;  // head g's window logits at wl_win[j * G + g]
   if constexpr (FUSED) {
     sel = nsplit == 1 && rr.t >= a.Natt - 1 && rr.t <= a.Nr + a.Ns - 2 && ksel < a.state_cap;
     if (sel && cnt_raw < ksel) {
@@ -1045,10 +1048,10 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   for (int g = nwaves - 1 - wave; g < G; g += nwaves) {
     if (a.wlog && !dense) {
       float* dst = a.wlog + (static_cast<size_t>(b) * a.Hq + kvh * G + g) * a.plan_cap + w0;
-      for (int i = lane; i < nws; i += 64) dst[i] = wl_s[g * KS + i];
+      for (int i = lane; i < nws; i += 64) dst[i] = wl_s[i * G + g];
     }
     if constexpr (FUSED && G > 1) {
-      if (sel) head_terms(lane, nwin, wl_win + g * KS);
+      if (sel) head_terms<G>(lane, nwin, wl_win + g);
     }
   }
   if constexpr (FUSED) {
@@ -1109,7 +1112,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     if (sel && wave == nwaves - 1) {
       int jbest;
       if constexpr (G > 1)
-        jbest = terms_argmin<G>(lane, nwin, [&](int g, int j) { return wl_win[g * KS + j]; });
+        jbest = terms_argmin<G>(lane, nwin, [&](int g, int j) { return wl_win[j * G + g]; });
       else
         jbest = window_argmin<1>(lane, nwin, [&](int, int j) { return wl_win[j]; });
       if (jbest < 0 || jbest >= nwin) jbest = 0;  // only for NaN logits
@@ -1278,7 +1281,9 @@ void launch_split(const Derived& d, const DecodeArgs& a, hipStream_t st, hipEven
   const int nw = KV::kBytes == 1 ? d.NW_fp8 : d.NW;
   const int block = 64 * nw;
   const uint32_t lds = (MF ? mf_lds_bytes<D, G>(nw) : 0u) +
-                       (a.mode != DSA_MODE_DENSE ? wl_lds_bytes(G, MF) : 0u) +
+                       (a.mode != DSA_MODE_DENSE
+                            ? wl_lds_bytes(G, MF ? a.wl_rows : max_fused_split(false))
+                            : 0u) +
                        (FUSED ? static_cast<uint32_t>(sizeof(uint32_t) * nw * a.words) : 0u);
   if constexpr (MF) {
     if (t0 || t1)

@@ -120,12 +120,28 @@ constexpr int kKeptReadCap = DSA_TUNE_KEPT_READ_CAP;
 // ahead of the position): in launches of few pairs, and in the others.
 constexpr int kKeptReadMax = 512;
 constexpr int kKeptReadMaxWide = 256;
-// One workgroup per (request, KV head), and no combine, in launches of at most
-// one pair per CU: the launch is bound by latency, and the second kernel costs
-// 3.3 us of it.  Vector-ALU tile,
-// sparse modes (32 to 256 pairs: 15-30% less per layer; at 512 pairs the
-// four-wave workgroups of the general kernel are 4% faster).
+// One workgroup per (request, KV head), and no combine, in sparse launches of
+// at most one pair per CU: the launch is bound by latency, and the second
+// kernel costs 3.3 us of it.  On the vector-ALU tile always (32 to 256 pairs:
+// 15-30% less per layer; at 512 pairs the four-wave workgroups of the general
+// kernel are 4% faster).  On the MFMA tile, whose eight waves take a tile or
+// two at a time, for at most kOneTilesMfma tiles of 32 rows (9 tiles, 8 pairs:
+// 10.7 -> 8.4 us) or at least kOnePairsMfma pairs (15 tiles: 128 pairs 15.1 ->
+// 13.6 us, 64 pairs 14.1 -> 13.8 us, but 32 pairs 11.0 -> 12.2 us: few CUs
+// then stream everything).
 constexpr int kOnePairs = 256;
+constexpr int kOneTilesMfma = 10;
+constexpr int kOnePairsMfma = 64;
+// Most waves of a sparse-mode MFMA workgroup.  A CU holds eight such waves
+// (256 registers each), so with eight the launch runs 256 workgroups at a time
+// and a second round for the rest; fewer waves make every workgroup resident
+// at once.  d = 128, eight waves -> this rule: 512 workgroups of 15 tiles
+// 29.4 -> 25.7 us (2 waves: 27.8), 768 of 8 tiles 31.3 -> 24.6 us (4 waves:
+// 27.9), 2048 of 9 tiles 76 -> 59.7 us (4 waves: 61.2).
+constexpr int waves_mfma(int64_t workgroups) {
+  const int w = workgroups <= 256 ? 8 : workgroups <= 512 ? 4 : 2;
+  return w < kWavesMfma ? w : kWavesMfma;
+}
 static_assert(kMaxFusedSplit % 64 == 0 && kMaxFusedSplit <= 1024, "fused split rows");
 static_assert(kMaxFusedSplitMfma % 64 == 0 && kMaxFusedSplitMfma <= 1024, "fused split rows");
 // Rows of one sparse-mode split at most, by tile.
@@ -187,6 +203,7 @@ struct DecodeArgs {
   float* wlog;           // window logits or nullptr
   float* part;           // split partials (S > 1)
   int B, Hq, Hkv, Lp, Ldec, mode, plan_cap, C, S;
+  int wl_rows;           // MFMA tile: window rows a split has at most (rounded up to 4)
   int ring;              // positions >= Ns rotate through this many slots (0: linear)
   int Ns;                // sink positions
   // fused step only: selection state (in/out) and plan (out)

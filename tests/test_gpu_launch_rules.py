@@ -1,6 +1,7 @@
 """The launch rules at their edges, each step (fused and as three calls)
 against the oracle: one workgroup per (request, KV head) with as many waves
-as it has tiles."""
+as it has tiles, and grouped-head workgroups of fewer waves where there are
+more of them than CUs."""
 
 import random
 
@@ -26,6 +27,15 @@ CASES = [
     ("wide_d64", 12, 5, 5, 64, 121, 20, 130, 41, 4, False, 6),
     ("wide_256_pairs", 16, 16, 16, 64, 41, 12, 60, 9, 0, False, 3),
     ("pairs_257", 257, 1, 1, 64, 41, 12, 60, 9, 0, False, 2),
+    # grouped heads: up to 10 tiles of 32 rows, or at least 64 pairs
+    ("mfma_10_tiles", 12, 8, 2, 128, 256, 24, 200, 64, 0, False, 8),
+    ("mfma_11_tiles", 12, 8, 2, 128, 257, 24, 200, 64, 0, True, 2),
+    ("mfma_63_pairs", 21, 6, 3, 64, 300, 24, 200, 90, 4, True, 4),
+    ("mfma_64_pairs", 16, 32, 4, 64, 300, 24, 200, 90, 4, False, 8),
+    # more workgroups than CUs: four waves, then two
+    ("mfma_257_pairs", 257, 2, 1, 64, 70, 12, 60, 9, 0, False, 4),
+    ("mfma_513_pairs", 513, 2, 1, 64, 70, 12, 60, 9, 0, False, 2),
+    ("mfma_g8_528_pairs", 33, 128, 16, 64, 70, 12, 100, 40, 4, False, 2),
 ]
 
 
