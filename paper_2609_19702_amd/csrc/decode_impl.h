@@ -114,6 +114,14 @@ struct KvFp8 {
 
 constexpr int kPre = 8;  // words per lane loaded ahead of the position (see PreRegs)
 
+// Where the fused step's kept window rows come from, by the build.
+enum class Kept {
+  kBitmap,  // each wave that owns window rows ranks a skip bitmap of its own
+  kList,    // the state's kept list (launch rule kept_read), else as kBitmap
+  kLong,    // skip lists longer than kLongSkips: the waves of the workgroup fill
+            // one bitmap together, and a wave ranks it word by word
+};
+
 // Keys of the (request, KV head) and the clamped decode position.
 struct RowRange {
   int n;      // keys; 0 for an unused slot
@@ -533,8 +541,10 @@ __host__ __device__ constexpr uint32_t mf_lds_bytes(int nw) {
   return mf_vt_bytes<D>(nw) + ((red + 15u) & ~15u);
 }
 
-template <class KV, int D, int G, int U, bool FUSED, bool KL, bool MF, int NWM>
+template <class KV, int D, int G, int U, bool FUSED, Kept KM, bool MF, int NWM>
 __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
+  constexpr bool KL = KM == Kept::kList;
+  constexpr bool LONG = FUSED && KM == Kept::kLong;
   constexpr int EPL = KV::kEpl;    // elements a lane loads per 16-byte access
   constexpr int LPR = D / EPL;     // lanes per row (V layout; K layout too without MF)
   constexpr int RPI = 64 / LPR;    // rows per load instruction
@@ -558,6 +568,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   float (*red)[G][D + 2] =
       reinterpret_cast<float (*)[G][D + 2]>(MF ? dyn_lds + mf_vt_bytes<D>(nw_launch) : smem);
   __shared__ int kp_s[FUSED ? KS : 1];  // fused: kept positions of the split
+  __shared__ int bad_s;  // kLong: a stored offset outside the window
   // MF: one V tile per wave (bf16, rows padded), read back transposed
   uint16_t* vt_w = reinterpret_cast<uint16_t*>(dyn_lds) + (threadIdx.x >> 6) * kMfmaTile * (D + kVPad);
   // Sparse mode: the split's window logits, head g of window row i at
@@ -638,7 +649,19 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     } else {
       may_rank = p0 + ((wave - p0) % nwaves + nwaves) % nwaves < p0 + wmax;
     }
-    load_pre<KL>(a, pair, lane, has_state && may_rank, preld);
+    if constexpr (LONG) {
+      // Every wave takes part: thread i of n loads entries i, i + n, ...
+      const uint16_t* off = a.st_off + static_cast<size_t>(pair) * a.state_cap;
+#pragma unroll
+      for (int i = 0; i < kPre; ++i) {
+        const int e = threadIdx.x + i * static_cast<int>(blockDim.x);
+        preld.w[i] = off[e < a.state_cap ? e : 0];
+      }
+      for (int w = threadIdx.x; w < a.words; w += blockDim.x) bm_all[w] = 0u;
+      if (threadIdx.x == 0) bad_s = 0;
+    } else {
+      load_pre<KL>(a, pair, lane, has_state && may_rank, preld);
+    }
   }
   // Settle the scalar values here, all at once: left alone, the compiler
   // sinks each load to its first use and waits for them one at a time.
@@ -758,6 +781,26 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   // nothing to rank, and a wave that issued a tile's loads ahead of its
   // ranking would stall at issue behind the CU's full memory queue and rank
   // late.
+  int kept_total = 0;
+  if constexpr (LONG) {
+    // The bits go in before the hoisted loads below, so that the wait for the
+    // entries counts nothing else.
+    if (Wn > 0) {
+      const int nvalid = min(max(rr.t - a.Natt + 1, 0), a.state_cap);
+      const int nuse = min(max(cnt_raw, 0), nvalid);
+      if (cnt_raw < nvalid) rep_flags |= DSA_FLAG_STATE_BEHIND;
+      __syncthreads();  // the bitmap is clear
+      bool bad = false;
+#pragma unroll
+      for (int i = 0; i < kPre; ++i) {
+        const int e = threadIdx.x + i * static_cast<int>(blockDim.x);
+        if (e < nuse) bad |= !set_skip(bm_all, static_cast<int>(preld.w[i]), a.Nr);
+      }
+      bad |= set_skips(bm_all, a.st_off + static_cast<size_t>(pair) * a.state_cap,
+                       threadIdx.x + kPre * static_cast<int>(blockDim.x), nuse, blockDim.x, a.Nr);
+      if (bad) bad_s = 1;
+    }
+  }
   constexpr bool kHoist = FUSED && !MF;
   typename KV::Raw kr[UU], vr[UU];  // the vector-ALU tile's K/V
   const bool pre = kHoist && wave < P;
@@ -783,6 +826,24 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     // whose list is missing) from a skip bitmap of the stored offsets in
     // the wave's own LDS slice.
     const int kneed = min(rr.t - (a.Natt - 1), a.state_cap);
+    if constexpr (LONG) {
+      if (Wn > 0) {
+        __syncthreads();  // every skipped offset is in the bitmap
+        if (jw0 < je) {
+          // A wave that owns window rows ranks them all (every such wave
+          // writes the same values), so none waits for another.
+          const int sk = min(a.Ns, rr.t + 1), hi = w0 + (r1 - wst);
+          const int dmax = min(rr.t - a.Ns, a.Nr - 1);
+          for (int r = w0 + lane; r < min(hi, sk); r += 64) kp_s[r - w0] = r;  // sinks
+          kept_total = rank_words(bm_all, rr.t, dmax, 0, dmax < 0 ? 0 : (dmax >> 5) + 1, sk, lane,
+                                  [&](int r, int p) {
+                                    if (r >= w0 && r < hi) kp_s[r - w0] = p;
+                                  });
+          if (bad_s) rep_flags |= DSA_FLAG_BAD_OFFSET;
+          fence_wave();
+        }
+      }
+    }
     from_list = KL && has_state && kneed >= 1 &&
                 ((kneed & 1) ? tags_raw.y : tags_raw.x) == kneed + 1 && cnt_raw >= kneed;
     if (from_list) {
@@ -807,7 +868,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
           kp_s[a.Ns + e - w0] = rr.t - static_cast<int>(list[e]);
       }
       fence_wave();
-    } else {
+    } else if constexpr (!LONG) {
       if (jw0 < je) {
         build_skip_set<KL>(a, pair, lane, rr.t, has_state ? cnt_raw : 0, bm_all + wave * a.words,
                        preld, ss);
@@ -822,11 +883,11 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     // live through the K/V loop (a kept list has the right count by
     // construction).
     if (reporter) {
-      rep_flags = rr.flags;
+      rep_flags |= rr.flags;
       if (rr.t >= 0 && !from_list) {
         rep_flags |= ss.flags;
-        const int kept = count_kept(ss, lane);
-        if (!(ss.flags & (DSA_FLAG_STATE_BEHIND | DSA_FLAG_BAD_OFFSET)) &&
+        const int kept = LONG ? kept_total : count_kept(ss, lane);
+        if (!(rep_flags & (DSA_FLAG_STATE_BEHIND | DSA_FLAG_BAD_OFFSET)) &&
             kept != min(rr.t + 1, a.Natt))
           rep_flags |= DSA_FLAG_COUNT;
       }
@@ -1136,10 +1197,10 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
 // One query head per KV head: four waves per SIMD stay resident (at most
 // 128 registers), so a small sparse layer runs as a single round of
 // workgroups.  (Larger groups keep their accumulators in registers instead.)
-template <class KV, int D, int G, int U, bool FUSED, bool KL>
+template <class KV, int D, int G, int U, bool FUSED, Kept KM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G == 1 ? 4 : 1, 8)))
 void decode_kernel(DecodeArgs a) {
-  decode_body<KV, D, G, U, FUSED, KL, false, kWaves>(a);
+  decode_body<KV, D, G, U, FUSED, KM, false, kWaves>(a);
 }
 
 // One query head per KV head, at most one (request, KV head) pair per CU: one
@@ -1150,18 +1211,18 @@ void decode_kernel(DecodeArgs a) {
 // rows and 8.1 us with 8), no barrier holds the prompt rows' V loads behind
 // the ranking, and nothing is left for a combine kernel (8.5 us per layer with
 // five splits per pair and the combine; LlamaGen-XL-like 8.1 -> 5.5 us).
-template <class KV, int D, bool FUSED, bool KL>
+template <class KV, int D, bool FUSED, Kept KM>
 __global__ __launch_bounds__(64 * kWavesWide) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void decode_wide_kernel(DecodeArgs a) {
-  decode_body<KV, D, 1, unroll_wide(D, KV::kBytes), FUSED, KL, false, kWavesWide>(a);
+  decode_body<KV, D, 1, unroll_wide(D, KV::kBytes), FUSED, KM, false, kWavesWide>(a);
 }
 
 // The grouped-head (MFMA) tile holds K and V of two 32-row tiles and the
 // output blocks in registers (up to 256 of them: two waves per SIMD).
-template <class KV, int D, int G, bool FUSED, bool KL>
+template <class KV, int D, int G, bool FUSED, Kept KM>
 __global__ __launch_bounds__(64 * kWavesMfma) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void decode_mfma_kernel(DecodeArgs a) {
-  decode_body<KV, D, G, 2, FUSED, KL, true, kWavesMfma>(a);
+  decode_body<KV, D, G, 2, FUSED, KM, true, kWavesMfma>(a);
 }
 
 // out = sum_s e^{m_s - M} acc_s / sum_s e^{m_s - M} l_s over the splits of
@@ -1274,7 +1335,7 @@ __global__ __launch_bounds__(kBlock + 64) void combine_select_kernel(DecodeArgs 
   }
 }
 
-template <class KV, int D, int G, int U, bool FUSED, bool KL, bool MF>
+template <class KV, int D, int G, int U, bool FUSED, Kept KM, bool MF>
 void launch_split(const Derived& d, const DecodeArgs& a, hipStream_t st, hipEvent_t t0,
                   hipEvent_t t1) {
   const int grid = d.B * d.Hkv * d.S;
@@ -1284,38 +1345,40 @@ void launch_split(const Derived& d, const DecodeArgs& a, hipStream_t st, hipEven
                        (a.mode != DSA_MODE_DENSE
                             ? wl_lds_bytes(G, MF ? a.wl_rows : max_fused_split(false))
                             : 0u) +
-                       (FUSED ? static_cast<uint32_t>(sizeof(uint32_t) * nw * a.words) : 0u);
+                       (FUSED ? static_cast<uint32_t>(sizeof(uint32_t) * a.words *
+                                                      (KM == Kept::kLong ? 1 : nw))
+                              : 0u);
   if constexpr (MF) {
     if (t0 || t1)
-      hipExtLaunchKernelGGL(decode_mfma_kernel<KV, D, G, FUSED, KL>, dim3(grid), dim3(block), lds,
+      hipExtLaunchKernelGGL(decode_mfma_kernel<KV, D, G, FUSED, KM>, dim3(grid), dim3(block), lds,
                             st, t0, t1, 0, a);
     else
-      decode_mfma_kernel<KV, D, G, FUSED, KL><<<grid, block, lds, st>>>(a);
+      decode_mfma_kernel<KV, D, G, FUSED, KM><<<grid, block, lds, st>>>(a);
   } else if (G == 1 && d.wide) {
     if (t0 || t1)
-      hipExtLaunchKernelGGL(decode_wide_kernel<KV, D, FUSED, KL>, dim3(grid), dim3(block), lds,
+      hipExtLaunchKernelGGL(decode_wide_kernel<KV, D, FUSED, KM>, dim3(grid), dim3(block), lds,
                             st, t0, t1, 0, a);
     else
-      decode_wide_kernel<KV, D, FUSED, KL><<<grid, block, lds, st>>>(a);
+      decode_wide_kernel<KV, D, FUSED, KM><<<grid, block, lds, st>>>(a);
   } else {
     if (t0 || t1)
-      hipExtLaunchKernelGGL(decode_kernel<KV, D, G, U, FUSED, KL>, dim3(grid), dim3(block), lds,
+      hipExtLaunchKernelGGL(decode_kernel<KV, D, G, U, FUSED, KM>, dim3(grid), dim3(block), lds,
                             st, t0, t1, 0, a);
     else
-      decode_kernel<KV, D, G, U, FUSED, KL><<<grid, block, lds, st>>>(a);
+      decode_kernel<KV, D, G, U, FUSED, KM><<<grid, block, lds, st>>>(a);
   }
 }
 
-template <class KV, int D, int G, bool FUSED, bool KL>
+template <class KV, int D, int G, bool FUSED, Kept KM>
 hipError_t launch_dg(const Derived& d, const DecodeArgs& a, hipStream_t st, hipEvent_t t0,
                      hipEvent_t t1) {
   // With several splits the stop event goes to the combine, so a timed call
   // covers every kernel it launches.
   const bool split = d.S > 1;
   if constexpr (uses_mfma_tile(G))
-    launch_split<KV, D, G, 2, FUSED, KL, true>(d, a, st, t0, split ? nullptr : t1);
+    launch_split<KV, D, G, 2, FUSED, KM, true>(d, a, st, t0, split ? nullptr : t1);
   else
-    launch_split<KV, D, G, unroll_of(G), FUSED, KL, false>(d, a, st, t0, split ? nullptr : t1);
+    launch_split<KV, D, G, unroll_of(G), FUSED, KM, false>(d, a, st, t0, split ? nullptr : t1);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !split) return e;
   if (FUSED) {
@@ -1336,14 +1399,14 @@ hipError_t launch_dg(const Derived& d, const DecodeArgs& a, hipStream_t st, hipE
   return hipGetLastError();
 }
 
-template <class KV, int D, bool FUSED, bool KL>
+template <class KV, int D, bool FUSED, Kept KM>
 hipError_t launch_d(const Derived& d, const DecodeArgs& a, hipStream_t st, hipEvent_t t0,
                     hipEvent_t t1) {
   switch (d.G) {
-    case 1: return launch_dg<KV, D, 1, FUSED, KL>(d, a, st, t0, t1);
-    case 2: return launch_dg<KV, D, 2, FUSED, KL>(d, a, st, t0, t1);
-    case 4: return launch_dg<KV, D, 4, FUSED, KL>(d, a, st, t0, t1);
-    default: return launch_dg<KV, D, 8, FUSED, KL>(d, a, st, t0, t1);
+    case 1: return launch_dg<KV, D, 1, FUSED, KM>(d, a, st, t0, t1);
+    case 2: return launch_dg<KV, D, 2, FUSED, KM>(d, a, st, t0, t1);
+    case 4: return launch_dg<KV, D, 4, FUSED, KM>(d, a, st, t0, t1);
+    default: return launch_dg<KV, D, 8, FUSED, KM>(d, a, st, t0, t1);
   }
 }
 
@@ -1352,17 +1415,19 @@ hipError_t launch_d(const Derived& d, const DecodeArgs& a, hipStream_t st, hipEv
 template <class KV>
 hipError_t launch_kv(const Derived& d, const DecodeArgs& a, hipStream_t st, hipEvent_t t0,
                      hipEvent_t t1, bool fused) {
-  // The fused step has two builds: with the kept lists of the selection
-  // state (launch rule kept_read) and without, so launches that keep no
-  // lists carry none of their code.
+  // The fused step has a build for each source of the kept rows, so no launch
+  // carries the code of another.
   if (fused && a.kept_read)
-    return d.D == 64 ? launch_d<KV, 64, true, true>(d, a, st, t0, t1)
-                     : launch_d<KV, 128, true, true>(d, a, st, t0, t1);
+    return d.D == 64 ? launch_d<KV, 64, true, Kept::kList>(d, a, st, t0, t1)
+                     : launch_d<KV, 128, true, Kept::kList>(d, a, st, t0, t1);
+  if (fused && a.state_cap > kLongSkips)
+    return d.D == 64 ? launch_d<KV, 64, true, Kept::kLong>(d, a, st, t0, t1)
+                     : launch_d<KV, 128, true, Kept::kLong>(d, a, st, t0, t1);
   if (fused)
-    return d.D == 64 ? launch_d<KV, 64, true, false>(d, a, st, t0, t1)
-                     : launch_d<KV, 128, true, false>(d, a, st, t0, t1);
-  return d.D == 64 ? launch_d<KV, 64, false, false>(d, a, st, t0, t1)
-                   : launch_d<KV, 128, false, false>(d, a, st, t0, t1);
+    return d.D == 64 ? launch_d<KV, 64, true, Kept::kBitmap>(d, a, st, t0, t1)
+                     : launch_d<KV, 128, true, Kept::kBitmap>(d, a, st, t0, t1);
+  return d.D == 64 ? launch_d<KV, 64, false, Kept::kBitmap>(d, a, st, t0, t1)
+                   : launch_d<KV, 128, false, Kept::kBitmap>(d, a, st, t0, t1);
 }
 
 }  // namespace

@@ -126,6 +126,19 @@ __device__ __forceinline__ int wave_allreduce(int x, Op op) {
   return op(__float_as_int(a), __float_as_int(b));
 }
 
+// Inclusive sum over the lanes 0 .. l of a wave: within rows of 16 lanes by DPP
+// row shifts, then the last lane of row 0 (2) into row 1 (3) and of row 1 into
+// rows 2 and 3.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return x;
+}
+
 __device__ __forceinline__ float wave_max(float x) {
   return wave_allreduce(x, [](float a, float b) { return fmaxf(a, b); });
 }
@@ -153,6 +166,73 @@ __device__ __forceinline__ void write_kept_list(int lane, int nwin, int jsel, in
   for (int r = lane; r < nwin; r += 64)
     if (r != jsel) kept[r < jsel ? r + 1 : r] = static_cast<uint16_t>(t - pos(r));
   if (lane == 0) *tag = k_next + 1;
+}
+
+// Kept sets of long skip lists, by a whole workgroup.
+//
+// Marks stored offset d as skipped in the LDS bitmap bm; false (and nothing
+// marked) for an offset outside [0, N_r - 2].
+__device__ __forceinline__ bool set_skip(uint32_t* bm, int d, int Nr) {
+  if (d > Nr - 2) return false;
+  atomicOr(&bm[d >> 5], 1u << (d & 31));
+  return true;
+}
+
+// Marks entries e, e + step, ... < n; returns whether any was out of range.
+// Eight loads are issued before the first is used (lists of thousands of
+// entries cost a memory latency per 8 * step entries and not per step).
+__device__ __forceinline__ bool set_skips(uint32_t* bm, const uint16_t* off, int e, int n,
+                                          int step, int Nr) {
+  constexpr int kBatch = 8;
+  bool bad = false;
+  for (; e < n; e += kBatch * step) {
+    int d[kBatch];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) d[i] = off[min(e + i * step, n - 1)];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i)
+      if (e + i * step < n) bad |= !set_skip(bm, d[i], Nr);
+  }
+  return bad;
+}
+
+// The offsets kept among word i of the window (offsets dmax .. 0, 32 to a
+// word, oldest word first): the bits bm leaves unmarked.
+__device__ __forceinline__ uint32_t kept_word(const uint32_t* bm, int dmax, int i) {
+  const uint32_t keep = ~bm[(dmax >> 5) - i];
+  return i == 0 ? keep & (0xffffffffu >> (31 - (dmax & 31))) : keep;
+}
+
+// Kept offsets in words [0, end) of the window.  Called by a whole wave.
+__device__ __forceinline__ int count_words(const uint32_t* bm, int dmax, int end, int lane) {
+  int n = 0;
+  for (int i = lane; i < end; i += 64) n += __popc(kept_word(bm, dmax, i));
+  return wave_allreduce(n, [](int a, int b) { return a + b; });
+}
+
+// Ranks the kept offsets of words [begin, end), oldest position first:
+// put(rank, position) for each, the first with rank `rank`; returns the rank
+// after the last.  A lane takes a word and a scan over the wave places it, so
+// the cost follows the words and the most offsets kept in one, not the window's
+// positions.  Called by a whole wave.
+template <typename Put>
+__device__ __forceinline__ int rank_words(const uint32_t* bm, int t, int dmax, int begin, int end,
+                                          int rank, int lane, Put put) {
+  for (int i0 = begin; i0 < end; i0 += 64) {
+    const int i = i0 + lane;
+    uint32_t keep = i < end ? kept_word(bm, dmax, i) : 0u;
+    const int c = __popc(keep);
+    const int x = wave_scan(c);
+    int r = rank + x - c;
+    const int p0 = t - 32 * ((dmax >> 5) - i);  // position of the word's offset 0
+    while (keep) {
+      const int b = 31 - __clz(keep);
+      keep &= ~(1u << b);
+      put(r++, p0 - b);
+    }
+    rank += __shfl(x, 63, 64);
+  }
+  return rank;
 }
 
 // (value, index) minimum with ties to the smaller index.

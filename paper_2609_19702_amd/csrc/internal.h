@@ -172,6 +172,18 @@ constexpr int unroll_for(int G, int d, int elem_bytes) {
 constexpr int unroll_wide(int d, int elem_bytes) {
   return cap_unroll(d == 128 && elem_bytes == 2 ? 4 : 5, d, elem_bytes);
 }
+// Skip lists longer than this are read and ranked by a whole workgroup (the
+// fused step where it keeps no lists, and plan): one wave reads them 64 entries
+// per memory latency past its first 512, and scans the window 64 positions at a
+// time.  Fused layers, one wave -> workgroup: 3635 entries 54 -> 41 us (16 x 32
+// heads), 1200 entries 29.8 -> 29.2 and 95 -> 89 us (512 and 2048 pairs), 160
+// grouped pairs 27.2 -> 26.0 us; 864 entries 32.0 -> 32.3 us, so not below.
+// In plan 1200 entries take 23.4 -> 22.0 us per step of three calls (64 pairs)
+// and 850 the same; past kPlanPairsMany pairs the chip is full either way and
+// 1200 entries lose 0.5%, so the line there is higher.
+constexpr int kLongSkips = 1024;
+constexpr int kLongSkipsMany = 1536;
+constexpr int kPlanPairsMany = 2048;
 constexpr int kMaxFusedWindow = 16384;  // N_r of the fused step (skip bitmap per wave in LDS)
 constexpr float kNegBig = -1.0e30f;  // "no score yet": finite, so exp2 of a difference is 0
 

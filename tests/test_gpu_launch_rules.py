@@ -35,6 +35,12 @@ CASES = [
     # more workgroups than CUs: four waves, then two
     ("mfma_257_pairs", 257, 2, 1, 64, 70, 12, 60, 9, 0, False, 4),
     ("mfma_513_pairs", 513, 2, 1, 64, 70, 12, 60, 9, 0, False, 2),
+    # skip lists of 1024 entries, and longer ones (no kept lists)
+    ("skips_1024", 17, 4, 4, 64, 20, 40, 1324, 300, 0, False, 9),
+    ("skips_1025", 17, 4, 4, 64, 20, 40, 1325, 300, 0, False, 9),
+    ("long_skips_d128", 17, 4, 4, 128, 20, 40, 1500, 310, 4, False, 16),
+    ("long_skips_mfma", 17, 8, 4, 128, 40, 40, 1500, 310, 4, False, 8),
+    ("long_skips_split", 17, 4, 4, 64, 20, 48, 1999, 560, 4, True, 4),
     ("mfma_g8_528_pairs", 33, 128, 16, 64, 70, 12, 100, 40, 4, False, 2),
 ]
 
@@ -77,3 +83,39 @@ def test_launch_rule_edges_match_oracle(case, kv_type):
     cnt, flg, idx = B.plan_views(p, s, fb.plan)
     rcnt, rflg, ridx = B.plan_views(p, s, sb.plan)
     assert torch.equal(cnt, rcnt) and torch.equal(flg, rflg) and torch.equal(idx, ridx)
+
+
+@pytest.mark.parametrize("heads", [(4, 4), (8, 4)])
+def test_long_skip_lists_report_bad_states(heads):
+    """A state with too few entries, one with an offset outside the window and
+    a repeated offset, each in a list of over 1024 entries: the fused step and
+    plan flag the same (request, KV head) pairs and keep the same rows."""
+    Hq, Hkv = heads
+    Bn, N_r, N_att, grid, d, Lp = 17, 1500, 310, 40, 64, 20
+    p = B.make_params(Lp, grid, grid, N_r, N_att)
+    s = B.make_shape(Bn, Hq, Hkv, d)
+    assert B.launch_info(p, s).kept_read == 0
+    ts = [1599, 1400, -1, 5000, 0] + [700 + 50 * i for i in range(Bn - 5)]
+    states, _ = c_replay_states(N_r, N_att, grid * grid, [min(t, 1599) for t in ts], Hkv,
+                                random.Random(5))
+    st0 = states_to_buffer(p, s, states, [min(t, 1599) for t in ts])
+    cnt, _, off = B.state_views(p, s, st0)
+    cnt[0] = 1100                    # request 0, head 0: 90 entries missing
+    off[1, 1150] = -1                # request 0, head 1: offset 65535
+    off[Hkv, 3] = off[Hkv, 4].clone()  # request 1, head 0: one offset twice
+    w = synth.Workload("longflags", 1, Bn, Hq, Hkv, d, Lp, grid, grid, N_r)
+    kv = synth.layer_kv(w, 0, DEV)
+    q = synth.layer_query(w, 0, DEV)
+    pos = torch.tensor(ts, dtype=torch.int32, device=DEV)
+    views = []
+    for fused in (True, False):
+        bufs, _ = run(p, s, q, kv, pos, st0, fused)
+        views.append(B.plan_views(p, s, bufs.plan))
+    (cnt, flg, idx), (rcnt, rflg, ridx) = views
+    assert torch.equal(cnt, rcnt) and torch.equal(flg, rflg)
+    want = torch.zeros(Bn, Hkv, dtype=torch.int32)
+    want[2], want[3] = B.FLAG_INACTIVE, B.FLAG_POS_CLAMPED
+    want[0, 0], want[0, 1], want[1, 0] = B.FLAG_STATE_BEHIND, B.FLAG_BAD_OFFSET, B.FLAG_COUNT
+    assert torch.equal(flg.cpu().view(Bn, Hkv), want)
+    # the fused step attends the first N_att of a bad set's rows, as plan lists them
+    assert torch.equal(idx, ridx)
