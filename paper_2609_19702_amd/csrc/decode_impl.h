@@ -154,6 +154,10 @@ __device__ __forceinline__ RowRange row_range_of(const DecodeArgs& a, int t, int
   return r;
 }
 
+__device__ __forceinline__ int pair_of(const DecodeArgs& a, int b, int kvh) {
+  return b * a.Hkv + kvh;
+}
+
 template <bool FUSED>
 __device__ __forceinline__ RowRange row_range(const DecodeArgs& a, int b, int pair) {
   return row_range_of<FUSED>(a, a.pos[b],
@@ -1225,47 +1229,93 @@ void decode_mfma_kernel(DecodeArgs a) {
   decode_body<KV, D, G, 2, FUSED, KM, true, kWavesMfma>(a);
 }
 
+// The partials of one (request, KV head, query head) that a wave loads before it
+// knows how many splits the request has: the first 64 splits' maxima and sums
+// (one split per lane) and the first kCombineAhead rows (lanes over columns).
+// Every slot of the launch's a.S splits is readable; one the request does not
+// have holds anything and is not used.
+constexpr int kCombineAhead = 8;
+
+template <int D>
+struct Partials {
+  const float* pp;
+  size_t sstride;
+  float m, l, x0[kCombineAhead], x1[kCombineAhead];
+};
+
+template <int D>
+__device__ __forceinline__ void load_partials(const DecodeArgs& a, int lane, int pair, int g, int G,
+                                              Partials<D>& p) {
+  p.pp = a.part + (static_cast<size_t>(pair) * a.S * G + g) * (D + 2);
+  p.sstride = static_cast<size_t>(G) * (D + 2);
+  const float* ml = p.pp + min(lane, a.S - 1) * p.sstride + D;
+  p.m = ml[0];
+  p.l = ml[1];
+#pragma unroll
+  for (int j = 0; j < kCombineAhead; ++j) {
+    const float* row = p.pp + min(j, a.S - 1) * p.sstride;
+    p.x0[j] = row[lane];
+    p.x1[j] = D == 128 ? row[(lane + 64) % D] : 0.f;
+  }
+}
+
 // out = sum_s e^{m_s - M} acc_s / sum_s e^{m_s - M} l_s over the splits of
 // (request b, query head g of KV head kvh), in base-2 exponents (the partial
-// maxima are kept in log2 units).  Called by one wave.
+// maxima are kept in log2 units).  Called by one wave.  Bound by its chain of
+// memory latencies: one for the position and the partials loaded ahead, and
+// one per kCombineAhead further splits.
 template <int D>
 __device__ __forceinline__ void combine_one(const DecodeArgs& a, int lane, int b, int kvh, int g,
-                                            int G, int nsplit) {
-  const int pair = b * a.Hkv + kvh;
-  const float* pp = a.part + (static_cast<size_t>(pair) * a.S * G + g) * (D + 2);
-  const size_t sstride = static_cast<size_t>(G) * (D + 2);
-  // Maxima and sums: one split per lane.
-  float M = kNegBig;
-  for (int s = lane; s < nsplit; s += 64) M = fmaxf(M, pp[s * sstride + D]);
+                                            int G, int nsplit, const Partials<D>& p) {
+  const float* pp = p.pp;
+  const size_t sstride = p.sstride;
+  constexpr int kA = kCombineAhead;
+  // Rows of splits j0 .. j0 + kA - 1 (past the last: its row again, weight 0).
+  float x0[kA], x1[kA], y0[kA], y1[kA];
+  auto load_rows = [&](int j0, float (&r0)[kA], float (&r1)[kA]) {
+#pragma unroll
+    for (int j = 0; j < kA; ++j) {
+      const float* row = pp + min(j0 + j, nsplit - 1) * sstride;
+      r0[j] = row[lane];
+      r1[j] = D == 128 ? row[(lane + 64) % D] : 0.f;
+    }
+  };
+  if (nsplit > kA) load_rows(kA, y0, y1);  // on their way while the maxima are reduced
+  const float m = lane < nsplit ? p.m : kNegBig;
+  float M = m;
+  for (int s = lane + 64; s < nsplit; s += 64) M = fmaxf(M, pp[s * sstride + D]);
   M = wave_max(M);
-  float L = 0.f;
-  for (int s = lane; s < nsplit; s += 64)
+  float w = fast_exp2(m - M);
+  float L = lane < nsplit ? p.l * w : 0.f;
+  for (int s = lane + 64; s < nsplit; s += 64)
     L = fmaf(pp[s * sstride + D + 1], fast_exp2(pp[s * sstride + D] - M), L);
   L = wave_sum(L);
-  // Weighted rows: lanes over columns, eight splits' loads in flight.
   float A0 = 0.f, A1 = 0.f;
-  for (int s0 = 0; s0 < nsplit; s0 += 64) {
-    const int sl = s0 + lane;
-    const float w = sl < nsplit ? fast_exp2(pp[sl * sstride + D] - M) : 0.f;
-    const int n = min(64, nsplit - s0);
-    for (int j0 = 0; j0 < n; j0 += 8) {
-      float x0[8], x1[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int sj = s0 + min(j0 + j, n - 1);
-        x0[j] = pp[sj * sstride + lane];
-        if constexpr (D == 128) x1[j] = pp[sj * sstride + lane + 64];
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float sw = j0 + j < n ? __shfl(w, j0 + j, 64) : 0.f;
-        A0 = fmaf(x0[j], sw, A0);
-        if constexpr (D == 128) A1 = fmaf(x1[j], sw, A1);
-      }
+  for (int j = 0; j < kA; ++j) {
+    x0[j] = j < nsplit ? p.x0[j] : 0.f;
+    x1[j] = j < nsplit ? p.x1[j] : 0.f;
+  }
+  for (int j0 = 0; j0 < nsplit; j0 += kA) {
+    if (j0 > 0 && j0 % 64 == 0) {  // weights of the next 64 splits
+      const int sl = j0 + lane;
+      w = sl < nsplit ? fast_exp2(pp[sl * sstride + D] - M) : 0.f;
     }
+#pragma unroll
+    for (int j = 0; j < kA; ++j) {
+      const float sw = j0 + j < nsplit ? __shfl(w, (j0 + j) & 63, 64) : 0.f;
+      A0 = fmaf(x0[j], sw, A0);
+      if constexpr (D == 128) A1 = fmaf(x1[j], sw, A1);
+    }
+#pragma unroll
+    for (int j = 0; j < kA; ++j) {
+      x0[j] = y0[j];
+      x1[j] = y1[j];
+    }
+    if (j0 + 2 * kA < nsplit) load_rows(j0 + 2 * kA, y0, y1);
   }
   float inv = L > 0.f ? 1.f / L : 0.f;
-  if (a.vs) inv *= a.vs[pair];
+  if (a.vs) inv *= a.vs[pair_of(a, b, kvh)];
   float* o = a.out + (static_cast<size_t>(b) * a.Hq + kvh * G + g) * D;
   o[lane] = A0 * inv;
   if constexpr (D == 128) o[lane + 64] = A1 * inv;
@@ -1279,47 +1329,80 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(DecodeArgs a, int G) {
   if (bh >= a.B * a.Hq) return;
   const int b = bh / a.Hq;
   const int h = bh % a.Hq;
+  Partials<D> p;
+  load_partials<D>(a, lane, pair_of(a, b, h / G), h % G, G, p);
   const RowRange rr = row_range<false>(a, b, b * a.Hkv + h / G);
   const int nsplit = (rr.n + a.C - 1) / a.C;
   if (nsplit <= 1) return;
-  combine_one<D>(a, lane, b, h / G, h % G, G, nsplit);
+  combine_one<D>(a, lane, b, h / G, h % G, G, nsplit, p);
 }
 
 // Fused step, several splits: one workgroup per (request, KV head).  Its
 // first min(G, 4) waves merge the splits of the group's query heads while
-// one more wave runs the phase-2 selection on the window logits and the plan
+// the other waves run the phase-2 selection on the window logits and the plan
 // the split workgroups wrote (the selection does not depend on the merged
-// outputs, so the two run side by side).
+// outputs, so the two run side by side): one wave for one head, or
+// select_waves(G), which turn a head each into its window softmax in LDS.
 constexpr int kCombineWaves = kWaves;
 
 template <int D, int G>
-__global__ __launch_bounds__(kBlock + 64) void combine_select_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(64 * (kCombineWaves + kSelectWaves))
+void combine_select_kernel(DecodeArgs a) {
   constexpr int CW = G < kCombineWaves ? G : kCombineWaves;
+  extern __shared__ __attribute__((aligned(16))) float terms[];  // [window key][G], if sel_lds
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int pair = blockIdx.x;
   const int b = pair / a.Hkv;
   const int kvh = pair % a.Hkv;
+  Partials<D> p;
+  if (wave < CW) load_partials<D>(a, lane, pair, wave, G, p);
   const RowRange rr = row_range<true>(a, b, pair);
   const int nsplit = (rr.n + a.C - 1) / a.C;
   if (nsplit <= 1) return;
   if (wave < CW) {
-    for (int g = wave; g < G; g += CW) combine_one<D>(a, lane, b, kvh, g, G, nsplit);
-    return;
+    combine_one<D>(a, lane, b, kvh, wave, G, nsplit, p);
+    for (int g = wave + CW; g < G; g += CW) {
+      load_partials<D>(a, lane, pair, g, G, p);
+      combine_one<D>(a, lane, b, kvh, g, G, nsplit, p);
+    }
   }
+  // The same for every wave from here to the barrier.
   const int t = rr.t;
-  if (t < a.Natt - 1 || t > a.Nr + a.Ns - 2) return;
   const int k = t - (a.Natt - 1);
-  if (k >= a.state_cap) return;
+  if (t < a.Natt - 1 || t > a.Nr + a.Ns - 2 || k >= a.state_cap) return;
   const int cnt = a.st_count[pair];
   if (cnt < k) {
-    if (lane == 0) a.st_flags[pair] |= DSA_FLAG_STATE_BEHIND;
+    if (wave == CW && lane == 0) a.st_flags[pair] |= DSA_FLAG_STATE_BEHIND;
     return;
   }
   const int nwin = rr.n - a.Lp - a.Ns;  // window keys after the sinks
   const float* wl = a.wlog + (static_cast<size_t>(b) * a.Hq + kvh * G) * a.plan_cap + a.Ns;
   const int plan_cap = a.plan_cap;
-  int jbest = window_argmin<G>(lane, nwin, [&](int g, int j) { return wl[g * plan_cap + j]; });
+  if constexpr (G > 1) {
+    if (a.sel_lds) {
+      for (int g = wave - CW; g >= 0 && g < G; g += select_waves(G)) {
+        float v[kRowRegs];
+        load_row(wl + g * plan_cap, lane, nwin, v);
+        head_terms_row<G>(lane, nwin, wl + g * plan_cap, v, terms + g);
+      }
+      __syncthreads();
+    }
+  }
+  if (wave != CW) return;
+  int jbest;
+  if constexpr (G > 1) {
+    jbest = a.sel_lds
+                ? terms_argmin<G>(lane, nwin, [&](int g, int j) { return terms[j * G + g]; })
+                : window_argmin<G>(lane, nwin,
+                                   [&](int g, int j) { return wl[g * plan_cap + j]; });
+  } else if (nwin > kSelectShort) {
+    float v[kRowRegs];
+    load_row(wl, lane, nwin, v);
+    jbest = row_argmin(lane, nwin, wl, v);
+  } else {
+    jbest = window_argmin<1>(lane, nwin, [&](int, int j) { return wl[j]; });
+  }
   if (jbest < 0 || jbest >= nwin) jbest = 0;  // only for NaN logits
   const int32_t* kept_pos = a.plan_idx + static_cast<size_t>(pair) * a.plan_cap + a.Ns;
   if (lane == 0) {
@@ -1383,11 +1466,12 @@ hipError_t launch_dg(const Derived& d, const DecodeArgs& a, hipStream_t st, hipE
   if (e != hipSuccess || !split) return e;
   if (FUSED) {
     constexpr int cw = G < kCombineWaves ? G : kCombineWaves;
+    const dim3 block(64 * (cw + select_waves(G)));
     if (t1)
-      hipExtLaunchKernelGGL(combine_select_kernel<D, G>, dim3(d.B * d.Hkv), dim3(64 * (cw + 1)), 0,
-                            st, nullptr, t1, 0, a);
+      hipExtLaunchKernelGGL(combine_select_kernel<D, G>, dim3(d.B * d.Hkv), block, a.sel_lds, st,
+                            nullptr, t1, 0, a);
     else
-      combine_select_kernel<D, G><<<d.B * d.Hkv, 64 * (cw + 1), 0, st>>>(a);
+      combine_select_kernel<D, G><<<d.B * d.Hkv, block, a.sel_lds, st>>>(a);
   } else {
     const int cgrid = (d.B * d.Hq + kWaves - 1) / kWaves;
     if (t1)

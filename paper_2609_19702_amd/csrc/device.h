@@ -442,6 +442,78 @@ __device__ __forceinline__ void head_terms(int lane, int n, float* row) {
   for (int j = lane; j < n; j += 64) row[j * STRIDE] = __expf(row[j * STRIDE] - mx[0]) * inv;
 }
 
+// The first 64 * kRowRegs values of a row of cap >= 1 values in memory, lane l's
+// c-th value row[l + 64 * c].  Loaded before the row's length is known (a
+// value past it is readable, and never used).
+constexpr int kRowRegs = 8;
+
+template <typename T>
+__device__ __forceinline__ void load_row(const T* row, int lane, int cap, T (&v)[kRowRegs]) {
+#pragma unroll
+  for (int c = 0; c < kRowRegs; ++c) v[c] = row[min(lane + 64 * c, cap - 1)];
+}
+
+// head_terms for a row in memory (src, its first values in v by load_row),
+// leaving the terms at dst[j * STRIDE].  Same operations, same order.
+template <int STRIDE>
+__device__ __forceinline__ void head_terms_row(int lane, int n, const float* src,
+                                               const float (&v)[kRowRegs], float* dst) {
+  float mx[1] = {-__builtin_inff()};
+  float sm[1] = {0.f};
+  const bool more = n > 64 * kRowRegs;
+#pragma unroll
+  for (int c = 0; c < kRowRegs; ++c)
+    if (lane + 64 * c < n) mx[0] = fmaxf(mx[0], v[c]);
+  if (more) {
+    for (int j0 = lane + 64 * kRowRegs; j0 < n; j0 += 64 * kRowRegs) {
+      float x[kRowRegs];
+      load_row(src + (j0 - lane), lane, n - (j0 - lane), x);
+#pragma unroll
+      for (int c = 0; c < kRowRegs; ++c)
+        if (j0 + 64 * c < n) {
+          dst[(j0 + 64 * c) * STRIDE] = x[c];
+          mx[0] = fmaxf(mx[0], x[c]);
+        }
+    }
+  }
+  wave_allreduce_n<1>(mx, [](float a, float b) { return fmaxf(a, b); });
+  float e[kRowRegs];
+#pragma unroll
+  for (int c = 0; c < kRowRegs; ++c) {
+    e[c] = __expf(v[c] - mx[0]);
+    if (lane + 64 * c < n) sm[0] += e[c];
+  }
+  if (more)
+    for (int j = lane + 64 * kRowRegs; j < n; j += 64) sm[0] += __expf(dst[j * STRIDE] - mx[0]);
+  wave_allreduce_n<1>(sm, [](float a, float b) { return a + b; });
+  const float inv = 1.f / sm[0];
+#pragma unroll
+  for (int c = 0; c < kRowRegs; ++c)
+    if (lane + 64 * c < n) dst[(lane + 64 * c) * STRIDE] = e[c] * inv;
+  if (more)
+    for (int j = lane + 64 * kRowRegs; j < n; j += 64)
+      dst[j * STRIDE] = __expf(dst[j * STRIDE] - mx[0]) * inv;
+}
+
+// window_argmin<1> for a row in memory (its first values in v by load_row).
+// For windows longer than window_argmin reads at once.
+__device__ __forceinline__ int row_argmin(int lane, int n, const float* src,
+                                          const float (&v)[kRowRegs]) {
+  float best = __builtin_inff();
+  int jbest = 0x7fffffff;
+#pragma unroll
+  for (int c = 0; c < kRowRegs; ++c)
+    if (lane + 64 * c < n) argmin_merge(best, jbest, v[c], lane + 64 * c);
+  for (int j0 = lane + 64 * kRowRegs; j0 < n; j0 += 64 * kRowRegs) {
+    float x[kRowRegs];
+    load_row(src + (j0 - lane), lane, n - (j0 - lane), x);
+#pragma unroll
+    for (int c = 0; c < kRowRegs; ++c)
+      if (j0 + 64 * c < n) argmin_merge(best, jbest, x[c], j0 + 64 * c);
+  }
+  return wave_argmin_key(best, jbest);
+}
+
 // terms_argmin: the argmin of sigma_j = sum over the group's heads g (in
 // order) of term(g, j), the terms head_terms left; the same index
 // window_argmin returns.  term(g, j) must be readable for every j < n.

@@ -185,6 +185,24 @@ constexpr int kLongSkips = 1024;
 constexpr int kLongSkipsMany = 1536;
 constexpr int kPlanPairsMany = 2048;
 constexpr int kMaxFusedWindow = 16384;  // N_r of the fused step (skip bitmap per wave in LDS)
+// Selection outside the decode kernel (select, and the combine of a split
+// request) over windows of more than kSelectShort keys, which one wave does not
+// read at once: with several heads per group, each of select_waves(G) waves
+// turns a head at a time into its window softmax in LDS and one sums and picks
+// (one wave for all heads reads every key three times, 64 per memory latency:
+// 8 heads, 410 keys, 92 pairs, select 9.4 -> 4.6 us; 922 keys of 4 heads, three
+// calls 48 -> 40 us).  Shorter windows stay on one wave: 29 keys, 512 pairs of
+// two heads, 16.5 us per step of three calls against 16.8.
+constexpr int kSelectShort = 256;
+constexpr int kSelectWaves = 4;
+constexpr int select_waves(int G) { return G < kSelectWaves ? G : kSelectWaves; }
+// LDS of those softmaxes for windows of at most cap keys; 0 (one wave, from
+// memory) for short windows, and where two workgroups' would not fit in a CU.
+constexpr uint32_t sel_lds_bytes(int G, int cap) {
+  return G > 1 && cap > kSelectShort && static_cast<int64_t>(G) * cap * 4 <= 65536
+             ? static_cast<uint32_t>(G * cap * 4)
+             : 0u;
+}
 constexpr float kNegBig = -1.0e30f;  // "no score yet": finite, so exp2 of a difference is 0
 
 struct PlanArgs {
@@ -229,6 +247,7 @@ struct DecodeArgs {
   uint16_t* st_kept;
   int Nr, Natt, state_cap, words, kept_cap;
   int kept_read;       // 1: kept lists are stored by the selection and read by the fused step
+  uint32_t sel_lds;    // combine: LDS of the group's window softmaxes (sel_lds_bytes)
 };
 
 struct SelectArgs {
@@ -242,6 +261,7 @@ struct SelectArgs {
   int32_t* st_kc;      // kept lists: tags [pairs][2] (k + 1, or 0) and lists
   uint16_t* st_kept;
   int pairs, Hq, Hkv, G, Ldec, Nr, Natt, Ns, plan_cap, state_cap, kept_cap, kept_stride;
+  uint32_t lds;        // LDS of the group's window softmaxes (sel_lds_bytes)
   int kept_on;         // 1: the state's kept lists are kept (the fused step's launch rule)
 };
 

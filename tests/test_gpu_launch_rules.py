@@ -41,6 +41,12 @@ CASES = [
     ("long_skips_d128", 17, 4, 4, 128, 20, 40, 1500, 310, 4, False, 16),
     ("long_skips_mfma", 17, 8, 4, 128, 40, 40, 1500, 310, 4, False, 8),
     ("long_skips_split", 17, 4, 4, 64, 20, 48, 1999, 560, 4, True, 4),
+    # selections outside the decode kernel: windows of 257 and of over 512 keys,
+    # and one whose softmaxes do not fit in LDS (2100 keys of eight heads)
+    ("select_257_g2", 12, 4, 2, 64, 300, 30, 500, 257, 0, True, 3),
+    ("select_600_g4", 12, 8, 2, 128, 40, 36, 1100, 600, 4, True, 3),
+    ("select_600_g1", 12, 2, 2, 128, 40, 36, 1100, 600, 4, True, 3),
+    ("select_2100_g8", 12, 8, 1, 64, 30, 48, 2300, 2100, 0, True, 5),
     ("mfma_g8_528_pairs", 33, 128, 16, 64, 70, 12, 100, 40, 4, False, 2),
 ]
 
@@ -119,3 +125,27 @@ def test_long_skip_lists_report_bad_states(heads):
     assert torch.equal(flg.cpu().view(Bn, Hkv), want)
     # the fused step attends the first N_att of a bad set's rows, as plan lists them
     assert torch.equal(idx, ridx)
+
+
+@pytest.mark.parametrize("d,heads,most", [(64, (2, 2), 73), (128, (4, 2), 42)])
+def test_dense_combine_of_many_splits(d, heads, most):
+    """Requests of 1, 8, 9, at most 64 and the most splits in one launch, over
+    a workspace of NaNs."""
+    Hq, Hkv = heads
+    grid, Lp, Bn = 96, 20, 6
+    L = grid * grid
+    pd = B.make_params(Lp, grid, grid, L, L, B.MODE_DENSE)
+    s = B.make_shape(Bn, Hq, Hkv, d)
+    info = B.launch_info(pd, s)
+    c = info.rows_per_split
+    assert info.max_splits == most
+    ts = [c - Lp - 1, 8 * c - Lp - 1, 8 * c - Lp, min(64 * c - Lp, L) - 1, L - 1, -1]
+    w = synth.Workload("splits", 1, Bn, Hq, Hkv, d, Lp, grid, grid, L, outlier_frac=0.01)
+    kv = synth.layer_kv(w, 0, DEV)
+    q = synth.layer_query(w, 0, DEV)
+    pos = torch.tensor(ts, dtype=torch.int32, device=DEV)
+    ws = torch.full((B.workspace_bytes(pd, s),), 0xFF, dtype=torch.uint8, device=DEV)  # NaN
+    out = torch.full((Bn, Hq, d), 7.0, device=DEV)
+    B.decode_attention(pd, s, q, kv.k, kv.v, B.kv_layout(kv.k), pos, None, d ** -0.5, out, None, ws)
+    check_layer_vs_oracle(pd, s, q, [request_arrays(kv, b, Lp) for b in range(Bn)], ts, None, None,
+                          out)
