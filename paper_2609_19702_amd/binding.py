@@ -153,12 +153,13 @@ def _ptr(x) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the handle of torch.cuda.current_stream() without the Stream object
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _nbytes(x) -> int:
-    return x.numel() * x.element_size()
+    return x.nbytes
 
 
 def _need(x, name, dtype=None, min_bytes=0, contiguous=True):
@@ -169,6 +170,9 @@ def _need(x, name, dtype=None, min_bytes=0, contiguous=True):
     read or write outside the tensor."""
     if x is None or isinstance(x, int):
         return
+    if (x.is_cuda and (dtype is None or x.dtype is dtype) and x.nbytes >= min_bytes
+            and x.is_contiguous()):
+        return  # the common case; what follows allows more, or names what is wrong
     if not x.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if dtype is not None and x.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
@@ -182,22 +186,53 @@ def _need(x, name, dtype=None, min_bytes=0, contiguous=True):
 _KV_DTYPES = (torch.bfloat16, torch.uint8, torch.float8_e4m3fn)
 
 
+# Sizes by the values of (params, shape): a call asks the library for them once
+# and not on every call (at most _SIZES_MOST entries are kept).
+_SIZES = {}
+_SIZES_MOST = 256
+
+
+def _sizes(p, s):
+    """(status, window logits bytes, plan bytes, state bytes or 0 where there is
+    no state); all sizes 0 where the status is not OK."""
+    key = bytes(p) + bytes(s)
+    z = _SIZES.get(key)
+    if z is None:
+        L = StateLayout()
+        st = lib().dsa_get_state_layout(C.byref(p), C.byref(s), C.byref(L))
+        z = (st, window_logits_count(p, s) * 4, plan_bytes(p, s), L.bytes if L.cap else 0)
+        if len(_SIZES) >= _SIZES_MOST:
+            _SIZES.clear()
+        _SIZES[key] = z
+    return z
+
+
+def _need_state(z, state):
+    _check(z[0], "dsa_get_state_layout")
+    _need(state, "state", None, z[3])
+
+
 def _check_decode_args(p, s, q, k, v, layout, decode_pos, out, window_logits):
+    """Returns the call's ``_sizes``."""
+    z = _sizes(p, s)
     B_, Hq, Hkv, d = s.batch, s.num_q_heads, s.num_kv_heads, s.head_dim
     _need(q, "q", torch.bfloat16, B_ * Hq * d * 2)
     _need(out, "out", torch.float32, B_ * Hq * d * 4)
     _need(decode_pos, "decode_pos", torch.int32, B_ * 4)
-    _need(window_logits, "window_logits", torch.float32, window_logits_count(p, s) * 4)
-    for x, name in ((k, "k"), (v, "v")):
-        _need(x, name, _KV_DTYPES, contiguous=False)
+    _need(window_logits, "window_logits", torch.float32, z[1])
+    _need(k, "k", _KV_DTYPES, contiguous=False)
+    _need(v, "v", _KV_DTYPES, contiguous=False)
     if isinstance(k, torch.Tensor) and isinstance(v, torch.Tensor):
-        if k.dtype != v.dtype or k.shape != v.shape or k.stride() != v.stride():
+        shape = k.shape
+        if k.dtype != v.dtype or shape != v.shape or k.stride() != v.stride():
             raise ValueError("k and v must share element type, shape and strides")
-        if k.dim() == 4 and layout.d_row_base is None:
+        if len(shape) == 4 and layout.d_row_base is None:
             rows_needed = p.prompt_len + (layout.ring_rows if layout.ring_rows else 1)
-            if k.shape[0] < B_ or k.shape[1] < Hkv or k.shape[3] != d or k.shape[2] < rows_needed:
-                raise ValueError(f"cache of shape {tuple(k.shape)} does not hold {B_} requests x "
+            nb, nh, rows, nd = shape
+            if nb < B_ or nh < Hkv or nd != d or rows < rows_needed:
+                raise ValueError(f"cache of shape {tuple(shape)} does not hold {B_} requests x "
                                  f"{Hkv} KV heads x {rows_needed}+ rows of {d} elements")
+    return z
 
 
 # ---- host-only helpers ------------------------------------------------------
@@ -270,9 +305,9 @@ def state_reset(p, s, state, req_mask=None, stream=None):
 
 def plan(p, s, decode_pos, state, plan_buf, stream=None):
     _need(decode_pos, "decode_pos", torch.int32, s.batch * 4)
-    _need(state, "state", None, state_bytes(p, s) if state_layout(p, s).cap else 0)
+    _need_state(_sizes(p, s), state)
     _check(lib().dsa_plan(C.byref(p), C.byref(s), _ptr(decode_pos), _ptr(state), _ptr(plan_buf),
-                          plan_buf.numel() * plan_buf.element_size(), _stream(stream)), "dsa_plan")
+                          _nbytes(plan_buf), _stream(stream)), "dsa_plan")
 
 
 def kv_layout(k: torch.Tensor, row_base: Optional[torch.Tensor] = None,
@@ -303,10 +338,10 @@ def decode_attention(p, s, q, k, v, layout: KVLayout, decode_pos, plan_buf, sm_s
     """``events``: optional (start, stop) pair from ``timing_events()``; they
     then receive the start of the split-K kernel and the end of the call's
     last kernel."""
-    _check_decode_args(p, s, q, k, v, layout, decode_pos, out, window_logits)
+    z = _check_decode_args(p, s, q, k, v, layout, decode_pos, out, window_logits)
     if p.mode != MODE_DENSE:
-        _need(plan_buf, "plan", None, plan_bytes(p, s))
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+        _need(plan_buf, "plan", None, z[2])
+    ws_bytes = 0 if workspace is None else _nbytes(workspace)
     args = (C.byref(p), C.byref(s), _ptr(q), _ptr(k), _ptr(v), C.byref(layout), _ptr(decode_pos),
             _ptr(plan_buf), float(sm_scale), _ptr(out), _ptr(window_logits), _ptr(workspace),
             ws_bytes)
@@ -320,10 +355,9 @@ def decode_attention(p, s, q, k, v, layout: KVLayout, decode_pos, plan_buf, sm_s
 def decode_step(p, s, q, k, v, layout: KVLayout, decode_pos, state, plan_buf, sm_scale, out,
                 window_logits, workspace=None, stream=None, events=None):
     """One fused decode step: plan + attention + selection in one pass."""
-    _check_decode_args(p, s, q, k, v, layout, decode_pos, out, window_logits)
-    _need(state, "state", None, state_bytes(p, s) if state_layout(p, s).cap else 0)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    pb = 0 if plan_buf is None else plan_buf.numel() * plan_buf.element_size()
+    _need_state(_check_decode_args(p, s, q, k, v, layout, decode_pos, out, window_logits), state)
+    ws_bytes = 0 if workspace is None else _nbytes(workspace)
+    pb = 0 if plan_buf is None else _nbytes(plan_buf)
     args = (C.byref(p), C.byref(s), _ptr(q), _ptr(k), _ptr(v), C.byref(layout), _ptr(decode_pos),
             _ptr(state), _ptr(plan_buf), pb, float(sm_scale), _ptr(out), _ptr(window_logits),
             _ptr(workspace), ws_bytes)
@@ -338,9 +372,8 @@ def decode_step_noalloc(p, s, q, k, v, layout: KVLayout, decode_pos, state, plan
                         out, window_logits, stream=None):
     """``decode_step`` without a workspace: the split partials live in the
     library's own per-GPU buffer (for callers that cannot allocate)."""
-    _check_decode_args(p, s, q, k, v, layout, decode_pos, out, window_logits)
-    _need(state, "state", None, state_bytes(p, s) if state_layout(p, s).cap else 0)
-    pb = 0 if plan_buf is None else plan_buf.numel() * plan_buf.element_size()
+    _need_state(_check_decode_args(p, s, q, k, v, layout, decode_pos, out, window_logits), state)
+    pb = 0 if plan_buf is None else _nbytes(plan_buf)
     _check(lib().dsa_decode_step_noalloc(C.byref(p), C.byref(s), _ptr(q), _ptr(k), _ptr(v),
                                          C.byref(layout), _ptr(decode_pos), _ptr(state),
                                          _ptr(plan_buf), pb, float(sm_scale), _ptr(out),
@@ -358,11 +391,13 @@ def timing_events():
 
 
 def select(p, s, decode_pos, plan_buf, window_logits, state, stream=None):
-    if state_layout(p, s).cap:
+    z = _sizes(p, s)
+    _check(z[0], "dsa_get_state_layout")
+    if z[3]:
         _need(decode_pos, "decode_pos", torch.int32, s.batch * 4)
-        _need(plan_buf, "plan", None, plan_bytes(p, s))
-        _need(window_logits, "window_logits", torch.float32, window_logits_count(p, s) * 4)
-        _need(state, "state", None, state_bytes(p, s))
+        _need(plan_buf, "plan", None, z[2])
+        _need(window_logits, "window_logits", torch.float32, z[1])
+        _need(state, "state", None, z[3])
     _check(lib().dsa_select(C.byref(p), C.byref(s), _ptr(decode_pos), _ptr(plan_buf),
                             _ptr(window_logits), _ptr(state), _stream(stream)), "dsa_select")
 
