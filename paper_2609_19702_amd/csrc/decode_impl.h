@@ -344,6 +344,17 @@ __device__ __forceinline__ uint32_t bf16_rne_bits(float x) {
   return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
 }
 
+// Plan-driven and dense grouped heads over fp8 caches of d = 128 keep one tile in
+// flight per wave instead of two: 129 registers and three waves per SIMD instead
+// of 212 and two.  32 requests of 8 dense KV heads (64x64 grid) 45.7 -> 42.5 us
+// per layer, 40 of 16 (48x48) 58.6 -> 56.1 us.  (bf16, or d = 64: 2-9% slower;
+// the fused step, whose eight-wave workgroups fill a CU alone, 4% slower on the
+// Emu3-like batch.)
+template <class KV, int D, bool FUSED>
+constexpr bool one_tile() {
+  return !FUSED && KV::kBytes == 1 && D == 128;
+}
+
 // Rows of a wave's V tile in LDS are D + kVPad bf16 apart: 32 bytes past a
 // multiple of 128, so the four rows one transposed read touches fall in
 // distinct banks.
@@ -1015,6 +1026,13 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
       mf_compute<KV, D, G>(a, lane, tr.rs, tr.re, tr.has_win, raw, qb, w0, sl, sl2, m_c, l_c,
                            oacc, wl_s, vt_w);
     };
+    if constexpr (one_tile<KV, D, FUSED>()) {
+      for (int j = jb; j < je; j += js) {
+        const TileRows ta = rows_of(j);
+        mf_load<KV, D>(a, lane, ta.rs, ta.re, ta.has_win, ta.pos_l, kmf, vb, ra);
+        compute(ta, ra);
+      }
+    } else
     for (int j = jb; j < je; j += 2 * js) {
       const TileRows ta = rows_of(j);
       mf_load<KV, D>(a, lane, ta.rs, ta.re, ta.has_win, ta.pos_l, kmf, vb, ra);
