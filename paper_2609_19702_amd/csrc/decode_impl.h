@@ -453,7 +453,7 @@ __device__ __forceinline__ void mf_compute(const DecodeArgs& a, int lane, int rs
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int r = rs + 16 * h + 4 * lq + j;
-        if (r < re) wls[(r - a.Lp - w0) * G + lr] = sc[h][j] * sl;
+        if (r < re) wls[lr * a.wl_rows + (r - a.Lp - w0)] = sc[h][j] * sl;
       }
   }
   // V rows of the tile into the wave's LDS tile, as bf16 (exact for fp8).
@@ -587,12 +587,14 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   // MF: one V tile per wave (bf16, rows padded), read back transposed
   uint16_t* vt_w = reinterpret_cast<uint16_t*>(dyn_lds) + (threadIdx.x >> 6) * kMfmaTile * (D + kVPad);
   // Sparse mode: the split's window logits, head g of window row i at
-  // wl_s[i * G + g] (dynamic LDS; none in dense mode).  The MFMA tile, whose
-  // workgroups share a CU only if their LDS fits, holds as many rows as a
-  // split can have; the vector-ALU tile always KS.
+  // wl_s[g * WS + i] (dynamic LDS; none in dense mode).  The MFMA tile, whose
+  // workgroups share a CU only if their LDS fits, holds as many rows per head
+  // as a split can have; the vector-ALU tile always KS.  (Head by head: with
+  // the heads of a row side by side the MFMA builds took 4-8 more registers,
+  // one of them a spill.)
+  const int WS = MF ? a.wl_rows : KS;
   float* wl_s = reinterpret_cast<float*>(dyn_lds + mf_bytes);
-  const uint32_t wl_bytes =
-      a.mode != DSA_MODE_DENSE ? wl_lds_bytes(G, MF ? a.wl_rows : KS) : 0u;
+  const uint32_t wl_bytes = a.mode != DSA_MODE_DENSE ? wl_lds_bytes(G, WS) : 0u;
   uint32_t* bm_all = reinterpret_cast<uint32_t*>(dyn_lds + mf_bytes + wl_bytes);
 
   const int lane = threadIdx.x & 63;
@@ -982,7 +984,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
         const int r = rs + u * RPI + rg;
         if (r < re) {
 #pragma unroll
-          for (int g = 0; g < G; ++g) wl_s[(r - a.Lp - w0) * G + g] = sc[u][g] * sl;
+          for (int g = 0; g < G; ++g) wl_s[g * WS + (r - a.Lp - w0)] = sc[u][g] * sl;
         }
       }
     }
@@ -1112,7 +1114,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   bool sel = false;
   const int ksel = rr.t - (a.Natt - 1);
   const int nwin = n - a.Lp - a.Ns;
-  float* const wl_win = wl_s + a.Ns * G;  // head g's window logits at wl_win[j * G + g]
+  float* const wl_win = wl_s + a.Ns;  // head g's window logits at wl_win[g * WS + j]
   if constexpr (FUSED) {
     sel = nsplit == 1 && rr.t >= a.Natt - 1 && rr.t <= a.Nr + a.Ns - 2 && ksel < a.state_cap;
     if (sel && cnt_raw < ksel) {
@@ -1131,10 +1133,10 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   for (int g = nwaves - 1 - wave; g < G; g += nwaves) {
     if (a.wlog && !dense) {
       float* dst = a.wlog + (static_cast<size_t>(b) * a.Hq + kvh * G + g) * a.plan_cap + w0;
-      for (int i = lane; i < nws; i += 64) dst[i] = wl_s[i * G + g];
+      for (int i = lane; i < nws; i += 64) dst[i] = wl_s[g * WS + i];
     }
     if constexpr (FUSED && G > 1) {
-      if (sel) head_terms<G>(lane, nwin, wl_win + g);
+      if (sel) head_terms(lane, nwin, wl_win + g * WS);
     }
   }
   if constexpr (FUSED) {
@@ -1195,7 +1197,7 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     if (sel && wave == nwaves - 1) {
       int jbest;
       if constexpr (G > 1)
-        jbest = terms_argmin<G>(lane, nwin, [&](int g, int j) { return wl_win[j * G + g]; });
+        jbest = terms_argmin<G>(lane, nwin, [&](int g, int j) { return wl_win[g * WS + j]; });
       else
         jbest = window_argmin<1>(lane, nwin, [&](int, int j) { return wl_win[j]; });
       if (jbest < 0 || jbest >= nwin) jbest = 0;  // only for NaN logits
@@ -1240,12 +1242,10 @@ void decode_wide_kernel(DecodeArgs a) {
 }
 
 // The grouped-head (MFMA) tile holds K and V of two 32-row tiles and the
-// output blocks in registers (up to 256 of them: two waves per SIMD; fp8 caches
-// of d = 64 read by a plan fit in 128, and 55 requests of 32 dense KV heads
-// take 45.6 us per layer at four waves per SIMD but 48.0 at three).
+// output blocks in registers (up to 256 of them: two waves per SIMD; the fp8
+// builds read by a plan fit in 128, four waves).
 template <class KV, int D, int G, bool FUSED, Kept KM>
-__global__ __launch_bounds__(64 * kWavesMfma) __attribute__((
-    amdgpu_waves_per_eu(D == 64 && KV::kBytes == 1 && !FUSED ? 4 : 2, 8)))
+__global__ __launch_bounds__(64 * kWavesMfma) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void decode_mfma_kernel(DecodeArgs a) {
   decode_body<KV, D, G, 2, FUSED, KM, true, kWavesMfma>(a);
 }

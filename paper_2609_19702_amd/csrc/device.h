@@ -402,13 +402,12 @@ __device__ __forceinline__ int window_argmin(int lane, int n, Logit logit) {
 // The selection of window_argmin (G > 1) in two parts, so the heads of a
 // group can be taken by different waves of a workgroup.
 //
-// head_terms: one head's window softmax, in place: row[j * STRIDE] (the logit
-// of window key j, 0 <= j < n) becomes exp(logit - max) / sum.  The maximum,
+// head_terms: one head's window softmax, in place: row[j] (the logit of
+// window key j, 0 <= j < n) becomes exp(row[j] - max) / sum.  The maximum,
 // the sum and the terms are the values window_argmin computes for the head
 // (same operations, same order).  Windows of up to kArgminRegs * 64 keys are
 // read into registers at once (every LDS read issued before the first use);
 // longer ones are streamed.  Called by a whole wave.
-template <int STRIDE>
 __device__ __forceinline__ void head_terms(int lane, int n, float* row) {
   float mx[1] = {-__builtin_inff()};
   float sm[1] = {0.f};
@@ -416,7 +415,7 @@ __device__ __forceinline__ void head_terms(int lane, int n, float* row) {
     float v[kArgminRegs], e[kArgminRegs];
 #pragma unroll
     for (int c = 0; c < kArgminRegs; ++c) {
-      const float x = row[min(lane + 64 * c, n - 1) * STRIDE];
+      const float x = row[min(lane + 64 * c, n - 1)];
       v[c] = lane + 64 * c < n ? x : -__builtin_inff();
     }
 #pragma unroll
@@ -431,15 +430,15 @@ __device__ __forceinline__ void head_terms(int lane, int n, float* row) {
     const float inv = 1.f / sm[0];
 #pragma unroll
     for (int c = 0; c < kArgminRegs; ++c)
-      if (lane + 64 * c < n) row[(lane + 64 * c) * STRIDE] = e[c] * inv;
+      if (lane + 64 * c < n) row[lane + 64 * c] = e[c] * inv;
     return;
   }
-  for (int j = lane; j < n; j += 64) mx[0] = fmaxf(mx[0], row[j * STRIDE]);
+  for (int j = lane; j < n; j += 64) mx[0] = fmaxf(mx[0], row[j]);
   wave_allreduce_n<1>(mx, [](float a, float b) { return fmaxf(a, b); });
-  for (int j = lane; j < n; j += 64) sm[0] += __expf(row[j * STRIDE] - mx[0]);
+  for (int j = lane; j < n; j += 64) sm[0] += __expf(row[j] - mx[0]);
   wave_allreduce_n<1>(sm, [](float a, float b) { return a + b; });
   const float inv = 1.f / sm[0];
-  for (int j = lane; j < n; j += 64) row[j * STRIDE] = __expf(row[j * STRIDE] - mx[0]) * inv;
+  for (int j = lane; j < n; j += 64) row[j] = __expf(row[j] - mx[0]) * inv;
 }
 
 // The first 64 * kRowRegs values of a row of cap >= 1 values in memory, lane l's
