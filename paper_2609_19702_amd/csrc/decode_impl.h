@@ -1362,8 +1362,9 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(DecodeArgs a, int G) {
 // first min(G, 4) waves merge the splits of the group's query heads while
 // the other waves run the phase-2 selection on the window logits and the plan
 // the split workgroups wrote (the selection does not depend on the merged
-// outputs, so the two run side by side): one wave for one head, or
-// select_waves(G), which turn a head each into its window softmax in LDS.
+// outputs, so the two run side by side): one wave for one head or a short
+// window, select_waves(G) for a long one (sel_lds), which turn a head each into
+// its window softmax in LDS, and none where there is no selection.
 constexpr int kCombineWaves = kWaves;
 
 template <int D, int G>
@@ -1487,7 +1488,8 @@ hipError_t launch_dg(const Derived& d, const DecodeArgs& a, hipStream_t st, hipE
   if (e != hipSuccess || !split) return e;
   if (FUSED) {
     constexpr int cw = G < kCombineWaves ? G : kCombineWaves;
-    const dim3 block(64 * (cw + select_waves(G)));
+    const int sw = a.state_cap == 0 ? 0 : a.sel_lds ? select_waves(G) : 1;
+    const dim3 block(64 * (cw + sw));
     if (t1)
       hipExtLaunchKernelGGL(combine_select_kernel<D, G>, dim3(d.B * d.Hkv), block, a.sel_lds, st,
                             nullptr, t1, 0, a);

@@ -4,6 +4,7 @@ C ABI, and moving selection states between the oracle's form (Algorithm 1's
 
 from __future__ import annotations
 
+import ctypes
 import math
 import sys
 
@@ -183,3 +184,34 @@ def c_replay_states(N_r, N_att, L, ts, Hkv, rng, threads=8):
         for b, h, st, kp in ex.map(one, jobs):
             states[b][h], kept[b][h] = st, kp
     return states, kept
+
+
+class _Dim3(ctypes.Structure):
+    _fields_ = [("x", ctypes.c_uint32), ("y", ctypes.c_uint32), ("z", ctypes.c_uint32)]
+
+
+class _KernelNodeParams(ctypes.Structure):  # hipKernelNodeParams
+    _fields_ = [("block", _Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", _Dim3), ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
+def launches(call):
+    """(workgroups, threads, dynamic LDS bytes) of each kernel that ``call()``
+    launches, in order, from the HIP graph it is captured into (never run)."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    call()  # loads the kernels
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        call()
+    graph = ctypes.c_void_p(g.raw_cuda_graph())
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        kp = _KernelNodeParams()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(kp)) == 0
+        out.append((kp.grid.x, kp.block.x, kp.lds))
+    return out
