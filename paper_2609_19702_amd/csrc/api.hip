@@ -171,7 +171,7 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d) {
       max_tiles = std::max(max_tiles, tiles_of(sp * C, std::min(rows_max, sp * C + C), tile_rows));
     const int cap = d->wide ? kWavesWide
                     : !d->MF ? kWavesValu
-                    : sparse ? waves_mfma(pairs * S)
+                    : sparse ? waves_mfma(pairs * S, d->D)
                              : kWavesMfmaDense;
     return static_cast<int>(std::min<int64_t>(cap, max_tiles));
   };

@@ -132,14 +132,24 @@ constexpr int kKeptReadMaxWide = 256;
 constexpr int kOnePairs = 256;
 constexpr int kOneTilesMfma = 10;
 constexpr int kOnePairsMfma = 64;
-// Most waves of a sparse-mode MFMA workgroup.  A CU holds eight such waves
-// (256 registers each), so with eight the launch runs 256 workgroups at a time
-// and a second round for the rest; fewer waves make every workgroup resident
-// at once.  d = 128, eight waves -> this rule: 512 workgroups of 15 tiles
-// 29.4 -> 25.7 us (2 waves: 27.8), 768 of 8 tiles 31.3 -> 24.6 us (4 waves:
-// 27.9), 2048 of 9 tiles 76 -> 59.7 us (4 waves: 61.2).
-constexpr int waves_mfma(int64_t workgroups) {
-  const int w = workgroups <= 256 ? 8 : workgroups <= 512 ? 4 : 2;
+// Most waves of a sparse-mode MFMA workgroup: as many as leave every workgroup of
+// the launch resident at once, so none waits for a second round.  A CU holds
+// kCuWavesMfma(d) waves of the fused builds (233 registers at most for d = 128
+// and 153 for d = 64: two and three waves per SIMD); past 1024 workgroups
+// (d = 128) or 1536 (d = 64) every choice runs in rounds and two waves measured
+// best or within 10% of it.  Fused layers of eight heads with 8, 4, 3 and 2
+// waves, d = 128: 512 workgroups of 15 tiles 31.5, 27.8, 29.0, 30.3 us; 768 of 8
+// tiles 32.0, 29.9, 32.1, 25.3; d = 64: 768 of 8 tiles 24.1, 16.4, 16.9, 18.2;
+// 1024 of 15 tiles in fp8 41.6, 32.4, 25.2, 28.4.  (Just past 256 workgroups the
+// second round is short: 264 of 15 tiles, bf16, d = 128, are 1-3% faster with
+// eight waves, of 8 tiles 8% slower.)  The plan-driven call has to add in the
+// order of the fused step, so it follows; it measured the same way but for fp8 of
+// d = 64, of which a CU holds 16 such waves: 512 workgroups of 15 tiles take
+// 13.0 us with eight waves and 14.6 with four (fused 22.6 and 18.7).
+constexpr int kCuWavesMfma(int d) { return d == 128 ? 8 : 12; }
+constexpr int waves_mfma(int64_t workgroups, int d) {
+  const auto resident = [&](int w) { return workgroups <= 256 * (kCuWavesMfma(d) / w); };
+  const int w = resident(8) ? 8 : resident(4) ? 4 : resident(3) ? 3 : 2;
   return w < kWavesMfma ? w : kWavesMfma;
 }
 static_assert(kMaxFusedSplit % 64 == 0 && kMaxFusedSplit <= 1024, "fused split rows");

@@ -59,3 +59,12 @@ def test_plan_driven_fp8_grouped_heads_keep_four_waves_per_simd(kernels):
     seen = {n: k["vgpr_count"] for n, k in kernels.items()
             if "decode_mfma_kernel" in n and "KvFp8" in n and "Lb0E" in n}
     assert len(seen) == 6 and max(seen.values()) <= 128, seen
+
+
+def test_grouped_head_waves_per_cu(kernels):
+    """The launch rule's waves per CU (four SIMDs of 512 registers): 8 of d = 128
+    and 12 of d = 64."""
+    for d, waves in ((128, 8), (64, 12)):
+        seen = [k["vgpr_count"] for n, k in kernels.items()
+                if "decode_mfma_kernel" in n and f"Li{d}E" in n]
+        assert len(seen) == 24 and max(seen) <= 512 // (waves // 4) // 8 * 8

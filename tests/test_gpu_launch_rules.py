@@ -1,7 +1,7 @@
 """The launch rules at their edges, each step (fused and as three calls)
 against the oracle: one workgroup per (request, KV head) with as many waves
-as it has tiles, and grouped-head workgroups of fewer waves where there are
-more of them than CUs."""
+as it has tiles, and grouped-head workgroups of fewer waves where that keeps
+every one resident."""
 
 import random
 
@@ -32,9 +32,14 @@ CASES = [
     ("mfma_11_tiles", 12, 8, 2, 128, 257, 24, 200, 64, 0, True, 2),
     ("mfma_63_pairs", 21, 6, 3, 64, 300, 24, 200, 90, 4, True, 4),
     ("mfma_64_pairs", 16, 32, 4, 64, 300, 24, 200, 90, 4, False, 8),
-    # more workgroups than CUs: four waves, then two
+    # more workgroups than CUs: four waves while every workgroup is resident,
+    # then three (d = 64) and two
     ("mfma_257_pairs", 257, 2, 1, 64, 70, 12, 60, 9, 0, False, 4),
-    ("mfma_513_pairs", 513, 2, 1, 64, 70, 12, 60, 9, 0, False, 2),
+    ("mfma_513_pairs", 513, 2, 1, 64, 70, 12, 60, 9, 0, False, 4),
+    ("mfma_769_pairs", 769, 2, 1, 64, 70, 12, 60, 9, 0, False, 3),
+    ("mfma_1025_pairs", 1025, 2, 1, 64, 70, 12, 60, 9, 0, False, 2),
+    ("mfma_d128_512_pairs", 512, 2, 1, 128, 70, 12, 60, 9, 0, False, 4),
+    ("mfma_d128_513_pairs", 513, 2, 1, 128, 70, 12, 60, 9, 0, False, 2),
     # skip lists of 1024 entries, and longer ones (no kept lists)
     ("skips_1024", 17, 4, 4, 64, 20, 40, 1324, 300, 0, False, 9),
     ("skips_1025", 17, 4, 4, 64, 20, 40, 1325, 300, 0, False, 9),
@@ -47,7 +52,7 @@ CASES = [
     ("select_600_g4", 12, 8, 2, 128, 40, 36, 1100, 600, 4, True, 3),
     ("select_600_g1", 12, 2, 2, 128, 40, 36, 1100, 600, 4, True, 3),
     ("select_2100_g8", 12, 8, 1, 64, 30, 48, 2300, 2100, 0, True, 5),
-    ("mfma_g8_528_pairs", 33, 128, 16, 64, 70, 12, 100, 40, 4, False, 2),
+    ("mfma_g8_528_pairs", 33, 128, 16, 64, 70, 12, 100, 40, 4, False, 4),
 ]
 
 
