@@ -556,6 +556,36 @@ __host__ __device__ constexpr uint32_t mf_lds_bytes(int nw) {
   return mf_vt_bytes<D>(nw) + ((red + 15u) & ~15u);
 }
 
+// Sums query head g's partials of the first nwaves <= N waves in lane j's columns
+// j and j + 64.  Every LDS read is issued before the first is used, with no
+// branches: slots past the workgroup's waves read its last wave again (the
+// maximum does not change) and add nothing (the waves are added in order).
+template <int N, int D, int G>
+__device__ __forceinline__ void merge_waves(const float (*red)[G][D + 2], int nwaves, int g,
+                                            int lane, float& M, float& L, float& A0, float& A1) {
+  float mw[N], lw[N], a0[N], a1[N];
+#pragma unroll
+  for (int w = 0; w < N; ++w) {
+    const int wr = min(w, nwaves - 1);
+    mw[w] = red[wr][g][D];
+    lw[w] = red[wr][g][D + 1];
+    a0[w] = red[wr][g][lane];
+    a1[w] = D == 128 ? red[wr][g][(lane + 64) % D] : 0.f;
+  }
+  M = kNegBig;
+#pragma unroll
+  for (int w = 0; w < N; ++w) M = fmaxf(M, mw[w]);
+  L = A0 = A1 = 0.f;
+#pragma unroll
+  for (int w = 0; w < N; ++w) {
+    const bool ok = w < nwaves;
+    const float sw = fast_exp2(mw[w] - M);
+    L = ok ? fmaf(lw[w], sw, L) : L;
+    A0 = ok ? fmaf(a0[w], sw, A0) : A0;
+    if constexpr (D == 128) A1 = ok ? fmaf(a1[w], sw, A1) : A1;
+  }
+}
+
 template <class KV, int D, int G, int U, bool FUSED, Kept KM, bool MF, int NWM>
 __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   constexpr bool KL = KM == Kept::kList;
@@ -1146,32 +1176,16 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
     }
   }
   // Merge the waves: wave w takes query heads w, w + nwaves, ... of the
-  // group, and lane j columns j and j + 64.  Every LDS read of a head is
-  // issued before the first is used, with no branches: slots past the
-  // workgroup's waves read its last wave again (the maximum does not
-  // change) and add nothing (the waves are added in order).
+  // group, and lane j columns j and j + 64.  Grouped-head workgroups of at most
+  // four waves read four slots and not eight (sparse launches of more than 256
+  // workgroups 2% less on average; decode_wide_kernel, 16 slots, lost 2% of its
+  // longer calls to the second copy of the merge).
   for (int g = wave; g < G; g += nwaves) {
-    float mw[NWM], lw[NWM], a0[NWM], a1[NWM];
-#pragma unroll
-    for (int w = 0; w < NWM; ++w) {
-      const int wr = min(w, nwaves - 1);
-      mw[w] = red[wr][g][D];
-      lw[w] = red[wr][g][D + 1];
-      a0[w] = red[wr][g][lane];
-      a1[w] = D == 128 ? red[wr][g][(lane + 64) % D] : 0.f;
-    }
-    float M = kNegBig;
-#pragma unroll
-    for (int w = 0; w < NWM; ++w) M = fmaxf(M, mw[w]);
-    float L = 0.f, A0 = 0.f, A1 = 0.f;
-#pragma unroll
-    for (int w = 0; w < NWM; ++w) {
-      const bool ok = w < nwaves;
-      const float sw = fast_exp2(mw[w] - M);
-      L = ok ? fmaf(lw[w], sw, L) : L;
-      A0 = ok ? fmaf(a0[w], sw, A0) : A0;
-      if constexpr (D == 128) A1 = ok ? fmaf(a1[w], sw, A1) : A1;
-    }
+    float M, L, A0, A1;
+    if (MF && nwaves <= 4)
+      merge_waves<4, D, G>(red, nwaves, g, lane, M, L, A0, A1);
+    else
+      merge_waves<NWM, D, G>(red, nwaves, g, lane, M, L, A0, A1);
     const int h = kvh * G + g;
     if (nsplit <= 1) {
       float inv = L > 0.f ? 1.f / L : 0.f;
@@ -1459,7 +1473,7 @@ void launch_split(const Derived& d, const DecodeArgs& a, hipStream_t st, hipEven
                             st, t0, t1, 0, a);
     else
       decode_mfma_kernel<KV, D, G, FUSED, KM><<<grid, block, lds, st>>>(a);
-  } else if (G == 1 && d.wide) {
+  } else if (G == 1 && (KV::kBytes == 1 ? d.wide_fp8 : d.wide)) {
     if (t0 || t1)
       hipExtLaunchKernelGGL(decode_wide_kernel<KV, D, FUSED, KM>, dim3(grid), dim3(block), lds,
                             st, t0, t1, 0, a);

@@ -29,6 +29,7 @@ struct Derived {
   int NW;         // waves per decode workgroup (1..kWaves), bf16 caches
   int NW_fp8;     // the same for fp8 caches (tiles of twice the rows)
   bool wide;      // one workgroup of up to kWavesWide waves per (request, KV head)
+  bool wide_fp8;  // the same on fp8 caches (false where kWaves waves hold its tiles)
   bool MF;        // grouped query heads on the MFMA tile (uses_mfma_tile(G))
   int kept_read;  // 1: selections store kept lists and the fused step reads its kept rows from them
   size_t ws_bytes;

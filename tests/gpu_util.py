@@ -196,8 +196,9 @@ class _KernelNodeParams(ctypes.Structure):  # hipKernelNodeParams
 
 
 def launches(call):
-    """(workgroups, threads, dynamic LDS bytes) of each kernel that ``call()``
-    launches, in order, from the HIP graph it is captured into (never run)."""
+    """(workgroups, threads, dynamic LDS bytes, kernel handle) of each kernel that
+    ``call()`` launches, in order, from the HIP graph it is captured into (never
+    run)."""
     hip = ctypes.CDLL("libamdhip64.so")
     call()  # loads the kernels
     torch.cuda.synchronize()
@@ -213,5 +214,5 @@ def launches(call):
     for node in nodes:
         kp = _KernelNodeParams()
         assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(kp)) == 0
-        out.append((kp.grid.x, kp.block.x, kp.lds))
+        out.append((kp.grid.x, kp.block.x, kp.lds, kp.func))
     return out

@@ -1,6 +1,6 @@
 """Launch shapes the library chooses for calls whose launch information does not
 say them (fp8 caches, the kernels after the split kernel), read from a captured
-graph: (workgroups, threads, dynamic LDS)."""
+graph: (workgroups, threads, dynamic LDS, kernel)."""
 
 import pytest
 import torch
@@ -44,4 +44,19 @@ def shapes(batch, heads, d, Lp, grid, N_r, N_att, mode=B.MODE_DIAGONAL, kv_type=
 def test_combine_has_the_waves_its_selection_needs(mode, N_r, N_att, selecting, lds):
     split, combine = shapes(8, (16, 4), 64, 480, 32, N_r, N_att, mode)
     assert split[0] > 8 * 4
-    assert combine == (8 * 4, 64 * (4 + selecting), lds)
+    assert combine[:3] == (8 * 4, 64 * (4 + selecting), lds)
+
+
+@pytest.mark.parametrize("d,rows", [(64, (150, 40)), (128, (120, 29))])
+@pytest.mark.parametrize("fused", [True, False])
+def test_fp8_launches_of_four_tiles_run_the_general_kernel(d, rows, fused):
+    """One workgroup per pair either way; more than four tiles take the kernel of
+    up to sixteen waves."""
+    def split(batch, Lp, N_att):
+        (got,) = shapes(batch, (4, 4), d, Lp, 24, 2 * N_att, N_att, kv_type="fp8", fused=fused)
+        assert got[0] == batch * 4
+        return got
+    few, many = split(17, *rows), split(129, *rows)  # neither keeps lists
+    assert few[1] == many[1] == 256 and few[3] == many[3]
+    longer = split(17, rows[0] + 64, rows[1])
+    assert longer[1] == 320 + 64 * (d == 128) and longer[3] != few[3]
