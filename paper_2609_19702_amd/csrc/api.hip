@@ -153,7 +153,8 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d) {
                    !(d->kept_read && pairs > kKeptReadPairs) &&
                    (d->MF ? tiles_of(0, rows_max, kMfmaTile) <= kOneTilesMfma ||
                                 pairs >= kOnePairsMfma
-                          : G == 1);
+                          : G == 1 && (d->D == 64 || rows_max <= kOneRows ||
+                                       pairs >= kOneRowsPairs));
   d->wide = one && !d->MF;
   d->wide_fp8 = false;
   if (one) {

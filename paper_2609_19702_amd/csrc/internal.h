@@ -125,12 +125,18 @@ constexpr int kKeptReadMaxWide = 256;
 // at most one pair per CU: the launch is bound by latency, and the second
 // kernel costs 3.3 us of it.  On the vector-ALU tile always (32 to 256 pairs:
 // 15-30% less per layer; at 512 pairs the four-wave workgroups of the general
-// kernel are 4% faster).  On the MFMA tile, whose eight waves take a tile or
+// kernel are 4% faster), but for few pairs of many rows of d = 128, where few
+// CUs would stream everything two tiles deep (rows over kOneRows, under
+// kOneRowsPairs pairs: 4 pairs of 502 rows 9.1 us split and 10.8 as one
+// workgroup each, 32 pairs read by a plan 9.0 and 9.8; 432 rows 8-9% faster
+// as one).  On the MFMA tile, whose eight waves take a tile or
 // two at a time, for at most kOneTilesMfma tiles of 32 rows (9 tiles, 8 pairs:
 // 10.7 -> 8.4 us) or at least kOnePairsMfma pairs (15 tiles: 128 pairs 15.1 ->
 // 13.6 us, 64 pairs 14.1 -> 13.8 us, but 32 pairs 11.0 -> 12.2 us: few CUs
 // then stream everything).
 constexpr int kOnePairs = 256;
+constexpr int kOneRows = 448;
+constexpr int kOneRowsPairs = 64;
 constexpr int kOneTilesMfma = 10;
 constexpr int kOnePairsMfma = 64;
 // Most waves of a sparse-mode MFMA workgroup: as many as leave every workgroup of

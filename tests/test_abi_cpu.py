@@ -215,3 +215,23 @@ def test_binding_rejects_bad_tensors_before_the_call():
         B.decode_step(p, s, q, k, k, lay, pos, None, None, 0.1, out, None)
     with pytest.raises(ValueError, match="GPU tensor"):
         B.plan(p, s, pos, None, torch.zeros(B.plan_bytes(p, s), dtype=torch.uint8))
+
+
+# Edges of the launch rules that send a sparse launch of few (request, KV head)
+# pairs to one workgroup per pair: (pairs, query heads per KV head, head_dim,
+# prompt rows, N_att) -> one split.
+ONE_WORKGROUP = [
+    ((32, 1, 128, 256, 192), True),   # 448 rows
+    ((32, 1, 128, 256, 193), False),  # longer: split for fewer than 64 pairs
+    ((63, 1, 128, 12, 490), False),
+    ((64, 1, 128, 12, 490), True),
+    ((4, 1, 64, 12, 490), True),
+]
+
+
+@pytest.mark.parametrize("shape,one", ONE_WORKGROUP)
+def test_one_workgroup_per_pair(shape, one):
+    pairs, G, d, Lp, n_att = shape
+    p = B.make_params(Lp, 40, 40, 2 * n_att, n_att)
+    li = B.launch_info(p, B.make_shape(pairs, G, 1, d))
+    assert (li.max_splits == 1) == one
