@@ -148,11 +148,14 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d) {
   // there too (70 pairs of 138 rows, d = 64: 10.1 -> 7.1 us), but their splits
   // and the combine that stores the lists are what the kept-list tests run.
   // Where N_att covers the whole image the rows are cut as in dense mode.
+  const int64_t tiles = tiles_of(0, rows_max, kMfmaTile);
   const bool one = sparse && p->n_att < ldec && pairs <= kOnePairs &&
                    rows_max <= max_fused_split(d->MF) &&
                    !(d->kept_read && pairs > kKeptReadPairs) &&
-                   (d->MF ? tiles_of(0, rows_max, kMfmaTile) <= kOneTilesMfma ||
-                                pairs >= kOnePairsMfma
+                   (d->MF ? tiles <= kOneTilesMfma ||
+                                (pairs >= kOnePairsMfma &&
+                                 !(pairs * S <= kOnePairs &&
+                                   (tiles > kOneTilesFull || (d->D == 128 && pairs < 128))))
                           : G == 1 && (d->D == 64 || rows_max <= kOneRows ||
                                        pairs >= kOneRowsPairs));
   d->wide = one && !d->MF;

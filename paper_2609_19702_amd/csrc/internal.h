@@ -131,14 +131,19 @@ constexpr int kKeptReadMaxWide = 256;
 // workgroup each, 32 pairs read by a plan 9.0 and 9.8; 432 rows 8-9% faster
 // as one).  On the MFMA tile, whose eight waves take a tile or
 // two at a time, for at most kOneTilesMfma tiles of 32 rows (9 tiles, 8 pairs:
-// 10.7 -> 8.4 us) or at least kOnePairsMfma pairs (15 tiles: 128 pairs 15.1 ->
-// 13.6 us, 64 pairs 14.1 -> 13.8 us, but 32 pairs 11.0 -> 12.2 us: few CUs
-// then stream everything).
+// 10.7 -> 8.4 us) or at least kOnePairsMfma pairs (under that few CUs would
+// stream everything: 32 pairs of 15 tiles 11.0 us split, 12.2 as one) whose
+// splits would not fit in one round of 256 workgroups (96 pairs of 15 tiles,
+// d = 128, eight heads: 18.9 us fused and 15.2 read by a plan split, 14.5 and
+// 11.7 as one).  Where they do (64 and 128 pairs) more than kOneTilesFull tiles
+// stay split (64 pairs of 16 tiles, d = 128, two heads, read by a plan 10.3 us
+// split, 13.5 as one), and of d = 128 also 64 pairs (15 tiles 10.0 and 12.2).
 constexpr int kOnePairs = 256;
 constexpr int kOneRows = 448;
 constexpr int kOneRowsPairs = 64;
 constexpr int kOneTilesMfma = 10;
 constexpr int kOnePairsMfma = 64;
+constexpr int kOneTilesFull = 15;
 // Most waves of a sparse-mode MFMA workgroup: as many as leave every workgroup of
 // the launch resident at once, so none waits for a second round.  A CU holds
 // kCuWavesMfma(d) waves of the fused builds (233 registers at most for d = 128

@@ -226,6 +226,18 @@ ONE_WORKGROUP = [
     ((63, 1, 128, 12, 490), False),
     ((64, 1, 128, 12, 490), True),
     ((4, 1, 64, 12, 490), True),
+    # grouped heads: 10 tiles of 32 rows; from 64 pairs, unless the splits fill
+    # the 256 CUs exactly (64 and 128 pairs) and have 16 tiles, or are 64 of d = 128
+    ((8, 4, 128, 160, 160), True),
+    ((8, 4, 128, 160, 161), False),
+    ((63, 2, 64, 256, 205), False),
+    ((64, 2, 64, 256, 205), True),
+    ((64, 2, 64, 64, 440), False),
+    ((64, 2, 128, 256, 205), False),
+    ((65, 2, 128, 256, 205), True),
+    ((128, 2, 128, 256, 205), True),
+    ((128, 2, 128, 64, 440), False),
+    ((129, 2, 128, 64, 440), True),
 ]
 
 
