@@ -344,15 +344,23 @@ __device__ __forceinline__ uint32_t bf16_rne_bits(float x) {
   return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
 }
 
-// Plan-driven and dense grouped heads over fp8 caches of d = 128 keep one tile in
-// flight per wave instead of two: 129 registers and three waves per SIMD instead
-// of 212 and two.  32 requests of 8 dense KV heads (64x64 grid) 45.7 -> 42.5 us
-// per layer, 40 of 16 (48x48) 58.6 -> 56.1 us.  (bf16, or d = 64: 2-9% slower;
-// the fused step, whose eight-wave workgroups fill a CU alone, 4% slower on the
-// Emu3-like batch.)
+// Plan-driven and dense grouped heads over fp8 caches of d = 128 have a second
+// build, with one tile in flight per wave instead of two: 128 registers and four
+// waves per SIMD instead of 206 and two (bf16, or d = 64: 2-9% slower).  Both add
+// the same numbers in the same order.  It serves launches that fill the chip
+// several times over: more than kOneTileDense dense splits (48 requests of 8 KV
+// heads, 1920 splits: 27.3 -> 24.6 us; 1536 splits 25.9 -> 22.4; 1152 splits 19.9
+// -> 21.1), more than 256 plan-driven workgroups (512 of 15 tiles 17.0 -> 16.6 us;
+// 256 of 15 11.2 -> 11.7).  The fused step keeps two: with one, 384 workgroups of
+// eight tiles took 50.7 us instead of 52.6 per four layers, but 512 of 15 tiles
+// 134 instead of 131 per eight.
 template <class KV, int D, bool FUSED>
-constexpr bool one_tile() {
+constexpr bool has_one_tile() {
   return !FUSED && KV::kBytes == 1 && D == 128;
+}
+constexpr int kOneTileDense = 1408;
+constexpr bool use_one_tile(bool dense, int workgroups) {
+  return workgroups > (dense ? kOneTileDense : 256);
 }
 
 // Rows of a wave's V tile in LDS are D + kVPad bf16 apart: 32 bytes past a
@@ -586,7 +594,8 @@ __device__ __forceinline__ void merge_waves(const float (*red)[G][D + 2], int nw
   }
 }
 
-template <class KV, int D, int G, int U, bool FUSED, Kept KM, bool MF, int NWM>
+// ONE: the MFMA tile with one tile in flight per wave (has_one_tile).
+template <class KV, int D, int G, int U, bool FUSED, Kept KM, bool MF, int NWM, bool ONE = false>
 __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   constexpr bool KL = KM == Kept::kList;
   constexpr bool LONG = FUSED && KM == Kept::kLong;
@@ -1058,18 +1067,11 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
       mf_compute<KV, D, G>(a, lane, tr.rs, tr.re, tr.has_win, raw, qb, w0, sl, sl2, m_c, l_c,
                            oacc, wl_s, vt_w);
     };
-    if constexpr (one_tile<KV, D, FUSED>()) {
-      for (int j = jb; j < je; j += js) {
-        const TileRows ta = rows_of(j);
-        mf_load<KV, D>(a, lane, ta.rs, ta.re, ta.has_win, ta.pos_l, kmf, vb, ra);
-        compute(ta, ra);
-      }
-    } else
-    for (int j = jb; j < je; j += 2 * js) {
+    for (int j = jb; j < je; j += (ONE ? 1 : 2) * js) {
       const TileRows ta = rows_of(j);
       mf_load<KV, D>(a, lane, ta.rs, ta.re, ta.has_win, ta.pos_l, kmf, vb, ra);
       const int j2 = j + js;
-      if (j2 < je) {
+      if (!ONE && j2 < je) {
         const TileRows tb = rows_of(j2);
         mf_load<KV, D>(a, lane, tb.rs, tb.re, tb.has_win, tb.pos_l, kmf, vb, rb);
         compute(ta, ra);
@@ -1257,11 +1259,11 @@ void decode_wide_kernel(DecodeArgs a) {
 
 // The grouped-head (MFMA) tile holds K and V of two 32-row tiles and the
 // output blocks in registers (up to 256 of them: two waves per SIMD; the fp8
-// builds read by a plan fit in 128, four waves).
-template <class KV, int D, int G, bool FUSED, Kept KM>
+// builds of d = 64 read by a plan fit in 128, four waves).
+template <class KV, int D, int G, bool FUSED, Kept KM, bool ONE>
 __global__ __launch_bounds__(64 * kWavesMfma) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void decode_mfma_kernel(DecodeArgs a) {
-  decode_body<KV, D, G, 2, FUSED, KM, true, kWavesMfma>(a);
+  decode_body<KV, D, G, 2, FUSED, KM, true, kWavesMfma, ONE>(a);
 }
 
 // The partials of one (request, KV head, query head) that a wave loads before it
@@ -1468,11 +1470,15 @@ void launch_split(const Derived& d, const DecodeArgs& a, hipStream_t st, hipEven
                                                       (KM == Kept::kLong ? 1 : nw))
                               : 0u);
   if constexpr (MF) {
+    auto kernel = decode_mfma_kernel<KV, D, G, FUSED, KM, false>;
+    if constexpr (has_one_tile<KV, D, FUSED>()) {
+      if (use_one_tile(a.mode == DSA_MODE_DENSE, grid))
+        kernel = decode_mfma_kernel<KV, D, G, FUSED, KM, true>;
+    }
     if (t0 || t1)
-      hipExtLaunchKernelGGL(decode_mfma_kernel<KV, D, G, FUSED, KM>, dim3(grid), dim3(block), lds,
-                            st, t0, t1, 0, a);
+      hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, st, t0, t1, 0, a);
     else
-      decode_mfma_kernel<KV, D, G, FUSED, KM><<<grid, block, lds, st>>>(a);
+      kernel<<<grid, block, lds, st>>>(a);
   } else if (G == 1 && (KV::kBytes == 1 ? d.wide_fp8 : d.wide)) {
     if (t0 || t1)
       hipExtLaunchKernelGGL(decode_wide_kernel<KV, D, FUSED, KM>, dim3(grid), dim3(block), lds,

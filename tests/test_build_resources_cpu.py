@@ -1,6 +1,6 @@
 """Registers of the built kernels, from the code objects' own metadata: no
-kernel spills a vector register or uses scratch memory, and the fp8 grouped-head
-builds read by a plan fit in 128 registers (four waves per SIMD)."""
+kernel spills a vector register or uses scratch memory, and the grouped-head
+builds keep the waves per SIMD that the launch rules count with."""
 
 import os
 import re
@@ -55,9 +55,10 @@ def test_no_kernel_spills(kernels):
 
 
 def test_plan_driven_fp8_grouped_heads_keep_four_waves_per_simd(kernels):
-    # decode_mfma_kernel<KvFp8, D, G, FUSED = false, ...>
+    # decode_mfma_kernel<KvFp8, D, G, FUSED = false, Kept, ONE>: d = 64, and the
+    # build of one tile in flight
     seen = {n: k["vgpr_count"] for n, k in kernels.items()
-            if "decode_mfma_kernel" in n and "KvFp8" in n and "Lb0E" in n}
+            if re.search(r"decode_mfma_kernel.*KvFp8E(Li64E.*Lb0E.*Lb0E|Li128E.*Lb0E.*Lb1E)", n)}
     assert len(seen) == 6 and max(seen.values()) <= 128, seen
 
 
@@ -67,4 +68,4 @@ def test_grouped_head_waves_per_cu(kernels):
     for d, waves in ((128, 8), (64, 12)):
         seen = [k["vgpr_count"] for n, k in kernels.items()
                 if "decode_mfma_kernel" in n and f"Li{d}E" in n]
-        assert len(seen) == 24 and max(seen) <= 512 // (waves // 4) // 8 * 8
+        assert len(seen) == (27 if d == 128 else 24) and max(seen) <= 512 // (waves // 4) // 8 * 8

@@ -7,7 +7,7 @@ import torch
 
 from paper_2609_19702_amd import binding as B
 from paper_2609_19702_amd import synth
-from tests.gpu_util import DEV, launches, say
+from tests.gpu_util import DEV, check_layer_vs_oracle, fp8_request_arrays, launches, say
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +60,31 @@ def test_fp8_launches_of_four_tiles_run_the_general_kernel(d, rows, fused):
     assert few[1] == many[1] == 256 and few[3] == many[3]
     longer = split(17, rows[0] + 64, rows[1])
     assert longer[1] == 320 + 64 * (d == 128) and longer[3] != few[3]
+
+
+def test_dense_fp8_builds_of_one_and_two_tiles_agree():
+    """48 requests (1920 splits) run the build with one tile in flight per wave, 24
+    of them (960) the one with two: the same outputs, bit for bit, and the oracle's."""
+    Bn, Hq, Hkv, d, Lp, grid = 48, 16, 8, 128, 100, 32
+    w = synth.Workload("dense_fp8", 1, Bn, Hq, Hkv, d, Lp, grid, grid, 64, outlier_frac=0.01)
+    kv = synth.to_fp8(synth.layer_kv(w, 0, DEV))
+    q = synth.layer_query(w, 0, DEV)
+    L = grid * grid
+    ts = [L - 1, 0, -1, 155, 156, 411] + [(37 * i) % L for i in range(Bn - 6)]
+    p = B.make_params(Lp, grid, grid, L, L, B.MODE_DENSE)
+    outs, kernels = [], []
+    for n in (Bn, Bn // 2):
+        s = B.make_shape(n, Hq, Hkv, d)
+        pos = torch.tensor(ts[:n], dtype=torch.int32, device=DEV)
+        bufs = B.alloc_buffers(p, s, DEV)
+        lay = B.kv_layout(kv.k, k_scale=kv.k_scale, v_scale=kv.v_scale)
+        split, _ = launches(lambda: B.decode_attention(
+            p, s, q, kv.k, kv.v, lay, pos, None, d ** -0.5, bufs.out, None, bufs.workspace))
+        torch.cuda.synchronize()
+        outs.append(bufs.out)
+        kernels.append(split)
+    assert kernels[0][0] == 1920 and kernels[1][0] == 960 and kernels[0][3] != kernels[1][3]
+    assert torch.equal(outs[0][:Bn // 2], outs[1])
+    check_layer_vs_oracle(p, B.make_shape(6, Hq, Hkv, d), q,
+                          [fp8_request_arrays(kv, b, Lp, Hkv) for b in range(6)], ts[:6], None,
+                          None, outs[1][:6])
