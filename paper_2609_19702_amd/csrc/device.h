@@ -212,9 +212,12 @@ __device__ __forceinline__ int count_words(const uint32_t* bm, int dmax, int end
 
 // Ranks the kept offsets of words [begin, end), oldest position first:
 // put(rank, position) for each, the first with rank `rank`; returns the rank
-// after the last.  A lane takes a word and a scan over the wave places it, so
-// the cost follows the words and the most offsets kept in one, not the window's
-// positions.  Called by a whole wave.
+// after the last.  A lane takes a word and a scan over the wave places it.  Then
+// each lane walks its word's kept offsets, so the cost follows the most kept in
+// one word; or, where few words keep many (a window that skips little yet, as in
+// the first N_att positions), the wave takes two words at a time, a lane per
+// offset (fused layers with nothing skipped yet, N_att 300, 512 pairs: 13.2 ->
+// 11.6 us).  Called by a whole wave.
 template <typename Put>
 __device__ __forceinline__ int rank_words(const uint32_t* bm, int t, int dmax, int begin, int end,
                                           int rank, int lane, Put put) {
@@ -225,12 +228,22 @@ __device__ __forceinline__ int rank_words(const uint32_t* bm, int t, int dmax, i
     const int x = wave_scan(c);
     int r = rank + x - c;
     const int p0 = t - 32 * ((dmax >> 5) - i);  // position of the word's offset 0
-    while (keep) {
-      const int b = 31 - __clz(keep);
-      keep &= ~(1u << b);
-      put(r++, p0 - b);
+    const int kept = __shfl(x, 63, 64), words = min(64, end - i0);
+    if (words * words <= 2 * kept) {
+      for (int k = 0; k < words; k += 2) {
+        const int w = k + (lane >> 5), b = 31 - (lane & 31);
+        const uint32_t kw = __shfl(keep, w, 64);
+        const int rw = __shfl(r, w, 64), pw = __shfl(p0, w, 64);
+        if ((kw >> b) & 1u) put(rw + __popc((kw >> b) >> 1), pw - b);
+      }
+    } else {
+      while (keep) {
+        const int b = 31 - __clz(keep);
+        keep &= ~(1u << b);
+        put(r++, p0 - b);
+      }
     }
-    rank += __shfl(x, 63, 64);
+    rank += kept;
   }
   return rank;
 }

@@ -206,6 +206,10 @@ constexpr int unroll_wide(int d, int elem_bytes) {
 constexpr int kLongSkips = 1024;
 constexpr int kLongSkipsMany = 1536;
 constexpr int kPlanPairsMany = 2048;
+// plan loads stored offsets ahead of the position in launches of at most this
+// many pairs; in larger ones the loads of requests that skip nothing yet cost
+// more than the latency.
+constexpr int kPlanAhead = 512;
 constexpr int kMaxFusedWindow = 16384;  // N_r of the fused step (skip bitmap per wave in LDS)
 // Selection outside the decode kernel (select, and the combine of a split
 // request) over windows of more than kSelectShort keys, which one wave does not

@@ -134,6 +134,29 @@ def test_long_skip_lists_report_bad_states(heads):
     assert torch.equal(idx, ridx)
 
 
+@pytest.mark.parametrize("N_r,N_att,grid", [
+    (1200, 90, 36),    # few words, each all kept, half kept, or nearly all skipped
+    (3300, 2100, 60),  # over 64 words: full ones first, then a remainder
+])
+def test_long_skip_plans_from_dense_to_sparse_windows(N_r, N_att, grid):
+    """plan where it ranks a long skip list's window by words, from the first
+    position (nothing skipped) to the last, against the oracle's kept positions."""
+    L = grid * grid
+    ts = sorted({t for t in (0, 1, 31, 32, 33, 62, 63, 64, 65, 95, N_att // 2, N_att - 1, N_att,
+                             N_att + 1, N_att + 40, (N_att + N_r) // 2, 2047, 2048, 2049,
+                             N_r - 1, N_r, L - 1) if t < L})
+    p, s = B.make_params(8, grid, grid, N_r, N_att), B.make_shape(len(ts), 2, 2, 64)
+    states, kept = c_replay_states(N_r, N_att, L, ts, 2, random.Random(N_r))
+    st = states_to_buffer(p, s, states, ts)
+    buf = torch.zeros(B.plan_bytes(p, s), dtype=torch.uint8, device=DEV)
+    B.plan(p, s, torch.tensor(ts, dtype=torch.int32, device=DEV), st, buf)
+    cnt, flg, idx = (x.cpu() for x in B.plan_views(p, s, buf))
+    assert not flg.any()
+    for pair in range(2 * len(ts)):
+        want = [int(x) for x in kept[pair // 2][pair % 2]]
+        assert idx[pair, :int(cnt[pair])].tolist() == want, (ts[pair // 2], pair % 2)
+
+
 @pytest.mark.parametrize("d,heads,most", [(64, (2, 2), 73), (128, (4, 2), 42)])
 def test_dense_combine_of_many_splits(d, heads, most):
     """Requests of 1, 8, 9, at most 64 and the most splits in one launch, over
