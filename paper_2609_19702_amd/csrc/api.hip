@@ -425,7 +425,8 @@ static dsa_status decode_impl(const dsa_params* p, const dsa_shape* s, const voi
   a.C = d.C;
   a.S = d.S;
   a.wl_rows = std::min(d.C, (d.plan_cap + 3) & ~3);  // C is a multiple of the tile
-  a.sel_lds = d.state_cap > 0 ? dsa::sel_lds_bytes(d.G, d.plan_cap - d.Ns) : 0u;
+  a.sel_lds = d.state_cap > 0 ? dsa::sel_lds_bytes(d.G, d.plan_cap - d.Ns, int64_t{d.B} * d.Hkv)
+                            : 0u;
   // No ring (0), or a ring of at least L_dec slots, maps every position to
   // itself; otherwise a.ring >= N_r > 0 slots rotate after the sinks.
   a.ring = (kv->ring_rows == 0 || kv->ring_rows >= d.Ldec)
@@ -594,7 +595,7 @@ DSA_API dsa_status dsa_select(const dsa_params* p, const dsa_shape* s, const int
   a.Ns = d.Ns;
   a.plan_cap = d.plan_cap;
   a.state_cap = d.state_cap;
-  a.lds = dsa::sel_lds_bytes(d.G, d.plan_cap - d.Ns);
+  a.lds = dsa::sel_lds_bytes(d.G, d.plan_cap - d.Ns, a.pairs);
   return hip_status(dsa::launch_select(d, a, stream));
 }
 

@@ -222,11 +222,19 @@ constexpr int kMaxFusedWindow = 16384;  // N_r of the fused step (skip bitmap pe
 constexpr int kSelectShort = 256;
 constexpr int kSelectWaves = 4;
 constexpr int select_waves(int G) { return G < kSelectWaves ? G : kSelectWaves; }
+// select loads ahead of the position in launches of at most this many pairs; in
+// larger ones the loads of requests that select nothing cost more than the
+// latency (2048 pairs, 500 keys, nothing selected: 3.45 us without, 3.85 with).
+constexpr int kSelectAhead = 1024;
 // LDS of those softmaxes for windows of at most cap keys; 0 (one wave, from
-// memory) for short windows, and where two workgroups' would not fit in a CU.
-constexpr uint32_t sel_lds_bytes(int G, int cap) {
-  return G > 1 && cap > kSelectShort && static_cast<int64_t>(G) * cap * 4 <= 65536
-             ? static_cast<uint32_t>(G * cap * 4)
+// memory) for short windows, where two workgroups' would not fit in a CU, and
+// where the launch's would not be resident at once and fewer than five fit in a
+// CU (64000 bytes: 512 pairs 47 -> 23 us, but 2048 pairs 59 -> 86; 32000 bytes,
+// 2048 pairs 44 -> 31).
+constexpr uint32_t sel_lds_bytes(int G, int cap, int64_t pairs) {
+  const int64_t lds = static_cast<int64_t>(G) * cap * 4;
+  return G > 1 && cap > kSelectShort && lds <= (pairs <= 512 ? 65536 : 32768)
+             ? static_cast<uint32_t>(lds)
              : 0u;
 }
 constexpr float kNegBig = -1.0e30f;  // "no score yet": finite, so exp2 of a difference is 0

@@ -20,10 +20,11 @@ namespace {
 
 // One wave per (request, KV head), or for long windows of several heads
 // (GROUP, sel_lds_bytes) a workgroup whose waves take the heads.  Bound by
-// latency.  Long windows (LONG, over kSelectShort keys) load the logits and the
-// plan row with the position and the counts, before those say how many there
-// are; short ones after them, since most requests select nothing.
-template <int G, bool GROUP, bool LONG>
+// latency.  Long windows (LONG, over kSelectShort keys) in launches of at most
+// kSelectAhead pairs (AHEAD) load the logits and the plan row with the position
+// and the counts, before those say how many there are; the others after them,
+// since most requests select nothing and then need none.
+template <int G, bool GROUP, bool LONG, bool AHEAD>
 __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs a) {
   extern __shared__ __attribute__((aligned(16))) float terms[];  // GROUP: [window key][G]
   const int lane = threadIdx.x & 63;
@@ -40,7 +41,7 @@ __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs a) {
   const int n = min(max(a.count[pair], 0), plan_cap);
   float v[kRowRegs];
   int32_t kp[kRowRegs];
-  if constexpr (LONG) {
+  if constexpr (AHEAD) {
     load_row(wl + (GROUP ? wave : 0) * plan_cap, lane, plan_cap - a.Ns, v);
     load_row(kept_pos, lane, plan_cap - a.Ns, kp);
   }
@@ -55,6 +56,7 @@ __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs a) {
   }
   const int nw = n - a.Ns;  // kept window keys after the sinks
   if (nw <= 0) return;
+  if constexpr (LONG && !AHEAD) load_row(wl + (GROUP ? wave : 0) * plan_cap, lane, nw, v);
   int jbest;
   if constexpr (GROUP) {
     head_terms_row<G>(lane, nw, wl + wave * plan_cap, v, terms + wave);
@@ -72,7 +74,7 @@ __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs a) {
   }
   if (jbest < 0 || jbest >= nw) jbest = 0;  // only for NaN logits
   int pos = 0;
-  if (LONG && jbest < 64 * kRowRegs) {
+  if (AHEAD && jbest < 64 * kRowRegs) {
 #pragma unroll
     for (int c = 0; c < kRowRegs; ++c)
       if (jbest >> 6 == c) pos = __shfl(kp[c], jbest & 63, 64);
@@ -94,13 +96,18 @@ __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs a) {
 
 template <int G>
 void launch_g(const SelectArgs& a, hipStream_t st) {
+  constexpr bool kGroup = G > 1;
   const int grid = (a.pairs + kWaves - 1) / kWaves;
-  if (G > 1 && a.lds)
-    select_kernel<G, G != 1, true><<<a.pairs, 64 * select_waves(G), a.lds, st>>>(a);
-  else if (G == 1 && a.plan_cap - a.Ns > kSelectShort)
-    select_kernel<G, false, G == 1><<<grid, kBlock, 0, st>>>(a);
+  if (kGroup ? a.lds == 0 : a.plan_cap - a.Ns <= kSelectShort) {
+    select_kernel<G, false, false, false><<<grid, kBlock, 0, st>>>(a);
+    return;
+  }
+  const auto kernel = a.pairs <= kSelectAhead ? select_kernel<G, kGroup, true, true>
+                                              : select_kernel<G, kGroup, true, false>;
+  if (kGroup)
+    kernel<<<a.pairs, 64 * select_waves(G), a.lds, st>>>(a);
   else
-    select_kernel<G, false, false><<<grid, kBlock, 0, st>>>(a);
+    kernel<<<grid, kBlock, 0, st>>>(a);
 }
 
 }  // namespace

@@ -62,6 +62,17 @@ def test_fp8_launches_of_four_tiles_run_the_general_kernel(d, rows, fused):
     assert longer[1] == 320 + 64 * (d == 128) and longer[3] != few[3]
 
 
+@pytest.mark.parametrize("batch,lds", [(64, 8 * 2000 * 4), (65, 0)])
+def test_select_of_many_pairs_keeps_its_lds_resident(batch, lds):
+    """Eight heads' softmaxes of 2000 keys: 64000 bytes per workgroup, for up to
+    512 pairs (two to a CU); past that one wave each, from memory."""
+    p, s = B.make_params(0, 70, 70, 4000, 2000), B.make_shape(batch, 64, 8, 64)
+    bufs = B.alloc_buffers(p, s, DEV)
+    pos = torch.full((batch,), -1, dtype=torch.int32, device=DEV)
+    (got,) = launches(lambda: B.select(p, s, pos, bufs.plan, bufs.logits, bufs.state))
+    assert got[2] == lds and got[0] == (batch * 8 if lds else batch * 8 // 4)
+
+
 def test_dense_fp8_builds_of_one_and_two_tiles_agree():
     """48 requests (1920 splits) run the build with one tile in flight per wave, 24
     of them (960) the one with two: the same outputs, bit for bit, and the oracle's."""
