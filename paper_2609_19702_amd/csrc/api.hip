@@ -143,15 +143,11 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d) {
     return (pe > r0 ? (pe - r0 + tile_rows - 1) / tile_rows : 0) +
            (r1 > wst ? (r1 - wst + tile_rows - 1) / tile_rows : 0);
   };
-  // One workgroup per pair (kOnePairs, internal.h).  Launches of more than
-  // kKeptReadPairs pairs that keep lists stay split: one workgroup is faster
-  // there too (70 pairs of 138 rows, d = 64: 10.1 -> 7.1 us), but their splits
-  // and the combine that stores the lists are what the kept-list tests run.
-  // Where N_att covers the whole image the rows are cut as in dense mode.
+  // One workgroup per pair (kOnePairs, internal.h).  Where N_att covers the whole
+  // image the rows are cut as in dense mode.
   const int64_t tiles = tiles_of(0, rows_max, kMfmaTile);
   const bool one = sparse && p->n_att < ldec && pairs <= kOnePairs &&
                    rows_max <= max_fused_split(d->MF) &&
-                   !(d->kept_read && pairs > kKeptReadPairs) &&
                    (d->MF ? tiles <= kOneTilesMfma ||
                                 (pairs >= kOnePairsMfma &&
                                  !(pairs * S <= kOnePairs &&

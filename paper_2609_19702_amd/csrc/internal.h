@@ -124,7 +124,7 @@ constexpr int kKeptReadMaxWide = 256;
 // One workgroup per (request, KV head), and no combine, in sparse launches of
 // at most one pair per CU: the launch is bound by latency, and the second
 // kernel costs 3.3 us of it.  On the vector-ALU tile always (32 to 256 pairs:
-// 15-30% less per layer; at 512 pairs the four-wave workgroups of the general
+// 15-30% less per layer, kept lists or not; at 512 pairs the four-wave workgroups of the general
 // kernel are 4% faster), but for few pairs of many rows of d = 128, where few
 // CUs would stream everything two tiles deep (rows over kOneRows, under
 // kOneRowsPairs pairs: 4 pairs of 502 rows 9.1 us split and 10.8 as one

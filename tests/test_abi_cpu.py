@@ -219,13 +219,16 @@ def test_binding_rejects_bad_tensors_before_the_call():
 
 # Edges of the launch rules that send a sparse launch of few (request, KV head)
 # pairs to one workgroup per pair: (pairs, query heads per KV head, head_dim,
-# prompt rows, N_att) -> one split.
+# prompt rows, N_att[, N_r, with kept lists]) -> one split.
 ONE_WORKGROUP = [
     ((32, 1, 128, 256, 192), True),   # 448 rows
     ((32, 1, 128, 256, 193), False),  # longer: split for fewer than 64 pairs
     ((63, 1, 128, 12, 490), False),
     ((64, 1, 128, 12, 490), True),
     ((4, 1, 64, 12, 490), True),
+    # also where the launch keeps lists (skip lists of over 512 entries)
+    ((72, 1, 128, 120, 115, 1152), True),
+    ((72, 4, 64, 120, 115, 1152), True),
     # grouped heads: 10 tiles of 32 rows; from 64 pairs, unless the splits fill
     # the 256 CUs exactly (64 and 128 pairs) and have 16 tiles, or are 64 of d = 128
     ((8, 4, 128, 160, 160), True),
@@ -243,7 +246,8 @@ ONE_WORKGROUP = [
 
 @pytest.mark.parametrize("shape,one", ONE_WORKGROUP)
 def test_one_workgroup_per_pair(shape, one):
-    pairs, G, d, Lp, n_att = shape
-    p = B.make_params(Lp, 40, 40, 2 * n_att, n_att)
+    pairs, G, d, Lp, n_att, *window = shape
+    p = B.make_params(Lp, 40, 40, window[0] if window else 2 * n_att, n_att)
     li = B.launch_info(p, B.make_shape(pairs, G, 1, d))
+    assert li.kept_read or not window
     assert (li.max_splits == 1) == one

@@ -82,9 +82,12 @@ def test_fused_equals_separate_calls(case):
 
 LIST_CASES = CASES[:4] + [
     # many (request, KV head) pairs and skip lists of 770-864 entries: lists on,
-    # three splits per request (the combine stores the next step's list)
+    # one workgroup per pair ...
     ("wide_gqa2", 1, 33, 4, 2, 64, 16, 40, 40, 1024),
     ("wide_mha", 1, 70, 1, 1, 64, 8, 36, 36, 900),
+    # ... and rows past one split (the combine stores the next step's list)
+    ("split_gqa2", 1, 33, 4, 2, 64, 400, 40, 40, 1024),
+    ("split_mha", 1, 70, 1, 1, 64, 420, 36, 36, 900),
     # few pairs with kept lists longer than the 256 offsets loaded ahead
     # (N_att 360 and 410; several splits per request)
     ("long_lists", 1, 40, 2, 1, 64, 16, 60, 60, 2048),
@@ -115,8 +118,8 @@ def test_fused_kept_list_equals_rebuild(case):
     # lists for launches of few pairs or long skip lists, of at most 256 kept offsets
     assert reads == ((Bn * Hkv <= 64 and lay.kept_cap <= 512)
                      or (lay.cap > 512 and lay.kept_cap <= 256))
-    if name.startswith("wide"):
-        assert reads and info.max_splits > 1
+    if name.startswith(("wide", "split")):
+        assert reads and (info.max_splits > 1) == name.startswith("split")
     if name.startswith("long"):
         assert reads and lay.kept_cap > 256
     say(name, "kept_cap", lay.kept_cap, "reads lists", reads, "positions", pos)
