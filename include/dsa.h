@@ -232,13 +232,13 @@ typedef struct dsa_launch_info {
   int32_t rows_per_split;  /* C: keys per split workgroup                   */
   int32_t max_splits;      /* S: splits per (request, KV head) at most      */
   int32_t workgroups;      /* B * Hkv * S                                   */
-  int32_t kernel_variant;  /* most K/V loads in flight per wave (2, 4 or 8), or 100
-                              for the MFMA tile of grouped query heads (32 rows) */
+  int32_t kernel_variant;  /* K/V loads in flight per wave (2, 4, 5 or 8) on a bf16
+                              cache, or 100 for the MFMA tile of grouped query
+                              heads (32 rows)                               */
   int32_t waves_per_group; /* waves per split workgroup (1..4; MFMA tile 1..8;
                               one workgroup per pair in launches of few pairs:
                               up to 16)                                     */
-  size_t workspace_bytes;  /* workspace a call asks for: at least the fp32
-                              partials the combine reads                    */
+  size_t workspace_bytes;  /* fp32 partials for the combine (0 with one split) */
   int32_t kept_read;       /* 1: selections keep the state's kept lists and
                               dsa_decode_step reads its kept window rows from
                               them when they match; a function of (params,
@@ -287,6 +287,8 @@ DSA_API dsa_status dsa_get_launch_info(const dsa_params* p, const dsa_shape* s,
 DSA_API size_t dsa_state_bytes(const dsa_params* p, const dsa_shape* s);
 DSA_API size_t dsa_plan_bytes(const dsa_params* p, const dsa_shape* s);
 DSA_API size_t dsa_workspace_bytes(const dsa_params* p, const dsa_shape* s);
+/* The workspace follows the launch shape and need not grow with the batch: a
+ * buffer shared by calls of several shapes holds the largest of their sizes. */
 /* Number of fp32 window logits per call: B * Hq * cap (plan cap). */
 DSA_API size_t dsa_window_logits_count(const dsa_params* p, const dsa_shape* s);
 

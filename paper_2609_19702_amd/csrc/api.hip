@@ -132,9 +132,6 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d) {
   C = std::max<int64_t>(block_rows, (C + block_rows - 1) / block_rows * block_rows);
   S = std::max<int64_t>(1, (rows_max + C - 1) / C);
   if (pairs * S > (int64_t(1) << 31) - 1) return DSA_ERR_INVALID_ARG;
-  // What callers allocate: sized for these splits, also where one workgroup
-  // per pair (below) needs none of it.
-  d->ws_bytes = S > 1 ? static_cast<size_t>(pairs) * S * G * (d->D + 2) * sizeof(float) : 0;
   // Tiles of rows [r0, r1): they stop at the prompt/decode boundary, so a
   // split can have one more than C / tile.
   auto tiles_of = [&](int64_t r0, int64_t r1, int64_t tile_rows) {
@@ -157,12 +154,13 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d) {
   d->wide = one && !d->MF;
   d->wide_fp8 = false;
   if (one) {
-    const int64_t unit = d->MF ? kMfmaTile : 64;
+    const int64_t unit = d->MF ? kMfmaTile : rows_per_instr * unroll_wide(d->D, 2);
     S = 1;
     C = std::max<int64_t>(unit, (rows_max + unit - 1) / unit * unit);
   }
   d->C = static_cast<int>(C);
   d->S = static_cast<int>(S);
+  d->ws_bytes = S > 1 ? static_cast<size_t>(pairs) * S * G * (d->D + 2) * sizeof(float) : 0;
   // Waves per workgroup: at most the most tiles any split has.  fp8 caches
   // load twice the elements per lane, so the vector-ALU tile holds twice the
   // rows (at most 64) and a split has fewer tiles.
@@ -270,7 +268,7 @@ DSA_API dsa_status dsa_get_launch_info(const dsa_params* p, const dsa_shape* s,
   out->rows_per_split = d.C;
   out->max_splits = d.S;
   out->workgroups = d.B * d.Hkv * d.S;
-  out->kernel_variant = d.MF ? 100 : d.U;
+  out->kernel_variant = d.MF ? 100 : d.wide ? dsa::unroll_wide(d.D, 2) : d.U;
   out->waves_per_group = d.NW;
   out->workspace_bytes = d.ws_bytes;
   out->kept_read = d.kept_read;

@@ -251,3 +251,17 @@ def test_one_workgroup_per_pair(shape, one):
     li = B.launch_info(p, B.make_shape(pairs, G, 1, d))
     assert li.kept_read or not window
     assert (li.max_splits == 1) == one
+    # what test_layouts_and_split_config states, at these shapes: a workspace only
+    # for splits, waves and loads as the launch has them
+    ws = pairs * li.max_splits * G * (d + 2) * 4 if li.max_splits > 1 else 0
+    assert li.workspace_bytes == ws == B.workspace_bytes(p, B.make_shape(pairs, G, 1, d))
+    if G > 1:
+        assert li.kernel_variant == 100 and 1 <= li.waves_per_group <= 8
+    elif one:
+        assert li.kernel_variant == (4 if d == 128 else 5)
+        tile = (512 // d) * li.kernel_variant
+        assert li.rows_per_split == -(-(Lp + n_att) // tile) * tile
+        tiles = -(-Lp // tile) + -(-n_att // tile)
+        assert li.waves_per_group == min(16, tiles)
+    else:
+        assert li.kernel_variant == 8 and 1 <= li.waves_per_group <= 4
