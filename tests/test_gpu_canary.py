@@ -114,6 +114,11 @@ EDGE = [
     ("fp8", B.MODE_DIAGONAL, 0, 4, 16, 2, 128, 33, 10, 30, 7, True, 0),
     ("fp8 ring", B.MODE_DIAGONAL, 0, 4, 8, 8, 64, 12, 10, 30, 7, True, 33),
     ("dense gqa", B.MODE_DENSE, 0, 3, 16, 2, 64, 300, 12, 100, 50, False, 0),
+    # several splits and the combine, by tile type
+    ("split mha", B.MODE_DIAGONAL, 0, 5, 4, 4, 64, 600, 12, 40, 10, False, 0),
+    ("split gqa+sinks", B.MODE_DIAGONAL, 4, 5, 8, 2, 128, 400, 12, 40, 12, False, 0),
+    ("split long gqa", B.MODE_DIAGONAL, 0, 4, 16, 2, 64, 20, 30, 700, 520, True, 0),
+    ("split window gqa", B.MODE_WINDOW, 4, 5, 8, 2, 128, 400, 12, 40, 12, False, 0),
 ]
 
 
@@ -131,6 +136,7 @@ def test_guards_edge_cases(case):
     q = synth.layer_query(w, 0, DEV)
     p = B.make_params(Lp, grid, grid, N_r, N_att, mode, S)
     s = B.make_shape(Bn, Hq, Hkv, d)
+    assert not tag.startswith("split") or B.launch_info(p, s).max_splits > 1
     om = {B.MODE_DIAGONAL: "diagonal_sink" if S else "diagonal", B.MODE_WINDOW: "streaming",
           B.MODE_DENSE: "diagonal"}[mode]
     st0 = None

@@ -27,7 +27,8 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # name, layers, batch, Hq, Hkv, d, L_p, gh, gw, window
     ("mha64", 2, 24, 8, 8, 64, 40, 16, 16, 64),
-    ("mha128_split", 2, 16, 4, 4, 128, 300, 12, 12, 100),
+    ("mha128_split", 2, 16, 4, 4, 128, 560, 12, 12, 100),
+    ("gqa4_split", 1, 8, 16, 4, 128, 440, 12, 12, 100),
     ("gqa4", 2, 10, 16, 4, 128, 64, 20, 20, 160),
     ("gqa8_d64", 1, 6, 16, 2, 64, 10, 8, 8, 40),
     ("gqa2_noprompt", 1, 9, 4, 2, 64, 0, 9, 9, 30),
@@ -51,6 +52,7 @@ def test_fused_equals_separate_calls(case):
     workload.build_histories(bt)
     info = B.launch_info(bt.p, bt.s)
     say(name, "splits", info.max_splits, "rows", info.rows_per_split, "n_att", bt.p.n_att)
+    assert not name.endswith("split") or info.max_splits > 1
     # separate calls on a copy of the state
     states = [Lr.bufs.state.clone() for Lr in bt.layers]
     workload.step(bt)
@@ -80,7 +82,7 @@ def test_fused_equals_separate_calls(case):
             assert torch.equal(lg_f[b, :, :n], lg_r[b, :, :n]), (li, b)
 
 
-LIST_CASES = CASES[:4] + [
+LIST_CASES = CASES[:5] + [
     # many (request, KV head) pairs and skip lists of 770-864 entries: lists on,
     # one workgroup per pair ...
     ("wide_gqa2", 1, 33, 4, 2, 64, 16, 40, 40, 1024),

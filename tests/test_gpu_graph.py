@@ -19,16 +19,18 @@ def snapshot(bt):
             for L in bt.layers]
 
 
-@pytest.mark.parametrize("mode,kv_heads,d", [
-    ("separate", 4, 128),  # plan -> attention -> select, grouped heads (MFMA tile)
-    ("dense", 4, 128),
-    ("fused", 4, 128),     # the fused step, grouped heads
-    ("fused", 8, 64),      # the fused step, one query head per KV head (vector-ALU tile)
+@pytest.mark.parametrize("mode,kv_heads,d,Lp", [
+    ("separate", 4, 128, 40),  # plan -> attention -> select, grouped heads (MFMA tile)
+    ("dense", 4, 128, 40),
+    ("fused", 4, 128, 40),     # the fused step, grouped heads
+    ("fused", 4, 128, 440),    # with several splits and the combine
+    ("fused", 8, 64, 40),      # the fused step, one query head per KV head (vector-ALU tile)
 ])
-def test_graph_replay_matches_eager(mode, kv_heads, d):
+def test_graph_replay_matches_eager(mode, kv_heads, d, Lp):
     dense, fused = mode == "dense", mode == "fused"
-    w = synth.Workload("graph", 3, 12, 8, kv_heads, d, 40, 12, 12, 48)
+    w = synth.Workload("graph", 3, 12, 8, kv_heads, d, Lp, 12, 12, 48)
     bt = workload.make_batch(w)
+    assert dense or (B.launch_info(bt.p, bt.s).max_splits > 1) == (Lp > 400)
     workload.build_histories(bt)
     workload.step(bt, dense=dense, fused=fused)
     torch.cuda.synchronize()

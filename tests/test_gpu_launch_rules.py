@@ -8,6 +8,7 @@ import random
 import pytest
 import torch
 
+from oracle import step as ostep
 from paper_2609_19702_amd import binding as B
 from paper_2609_19702_amd import synth
 from tests.gpu_util import (DEV, c_replay_states, check_layer_vs_oracle, fp8_request_arrays,
@@ -96,6 +97,47 @@ def test_launch_rule_edges_match_oracle(case, kv_type):
     cnt, flg, idx = B.plan_views(p, s, fb.plan)
     rcnt, rflg, ridx = B.plan_views(p, s, sb.plan)
     assert torch.equal(cnt, rcnt) and torch.equal(flg, rflg) and torch.equal(idx, ridx)
+
+
+WINDOW_CASES = [
+    # name, B, Hq, Hkv, d, L_p, grid, N_att, sinks, splits > 1
+    ("wide", 12, 3, 3, 128, 225, 12, 16, 0, False),
+    ("mha_split", 12, 2, 2, 64, 500, 12, 40, 4, True),
+    ("mfma_10_tiles", 12, 8, 2, 128, 256, 14, 64, 0, False),
+    ("mfma_11_tiles", 12, 8, 2, 128, 257, 14, 64, 4, True),
+    ("mfma_513_pairs", 513, 2, 1, 64, 70, 12, 9, 0, False),
+]
+
+
+@pytest.mark.parametrize("kv_type", ["bf16", "fp8"])
+@pytest.mark.parametrize("case", WINDOW_CASES, ids=[c[0] for c in WINDOW_CASES])
+def test_launch_rule_edges_in_window_mode(case, kv_type):
+    name, Bn, Hq, Hkv, d, Lp, grid, N_att, sinks, split = case
+    L = grid * grid
+    p = B.make_params(Lp, grid, grid, N_att, N_att, B.MODE_WINDOW, sinks)
+    s = B.make_shape(Bn, Hq, Hkv, d)
+    assert (B.launch_info(p, s).max_splits > 1) == split
+    ts = positions(Bn, L, N_att, N_att, seed=Bn + d)
+    w = synth.Workload(name, 1, Bn, Hq, Hkv, d, Lp, grid, grid, N_att, outlier_frac=0.01)
+    kv = synth.layer_kv(w, 0, DEV)
+    arrays_of = lambda b: request_arrays(kv, b, Lp)  # noqa: E731
+    if kv_type == "fp8":
+        kv = synth.to_fp8(kv)
+        arrays_of = lambda b: fp8_request_arrays(kv, b, Lp, Hkv)  # noqa: E731
+    q = synth.layer_query(w, 0, DEV)
+    states = [ostep.random_states(Hkv, N_att, N_att, max(t, 0), [0] * (Hkv * L), "streaming", sinks)
+              for t in ts]
+    pos = torch.tensor(ts, dtype=torch.int32, device=DEV)
+    lay = B.kv_layout(kv.k, k_scale=kv.k_scale, v_scale=kv.v_scale)
+    st0 = torch.zeros(B.state_bytes(p, s), dtype=torch.uint8, device=DEV)
+    arrays = [arrays_of(b) for b in range(Bn)]
+    outs = []
+    for fused in (True, False):
+        bufs, _ = run(p, s, q, kv, pos, st0, fused, lay)
+        check_layer_vs_oracle(p, s, q, arrays, ts, states, bufs.plan, bufs.out, None,
+                              bufs.logits if kv_type == "bf16" else None)
+        outs.append(bufs.out)
+    assert torch.equal(*outs)
 
 
 @pytest.mark.parametrize("heads", [(4, 4), (8, 4)])

@@ -27,6 +27,7 @@ CASES = [
     (6, 8, 8, 64, 0, 12, 12, 40, 10, 47),
     (5, 8, 2, 128, 33, 10, 10, 30, 7, 30),
     (4, 16, 2, 64, 8, 9, 9, 24, 24, 29),
+    (5, 8, 2, 128, 440, 10, 10, 30, 7, 30),  # several splits
 ]
 
 

@@ -164,3 +164,67 @@ def test_fused_grouped_selection_single_split(case):
     forced = check_layer_vs_oracle(p, s, q, arrays, ts, states, fb.plan, fb.out, fst, fb.logits)
     say(f"  near-tie picks adopted: {forced}")
     assert forced <= 2
+
+
+@pytest.mark.parametrize("N_att", [200, 256, 257, 600, 2100])
+@pytest.mark.parametrize("G", [1, 4, 8])
+def test_select_of_infinite_and_nan_logits(G, N_att):
+    """Windows read at once, by a wave per head and from memory (eight heads of
+    2100 keys) treat special logits alike: a key of -inf has no weight and is
+    dropped first; +inf or NaN among several heads leaves every score NaN and the
+    oldest key goes; one head orders its logits, and NaN is never the least."""
+    grid, Bn = 50, 6
+    p, s = B.make_params(0, grid, grid, N_att + 40, N_att), B.make_shape(Bn, G, 1, 64)
+    bufs = B.alloc_buffers(p, s, DEV)
+    pos = torch.full((Bn,), N_att - 1, dtype=torch.int32, device=DEV)  # every position is kept
+    B.plan(p, s, pos, bufs.state, bufs.plan)
+    wl = bufs.logits.view(Bn, G, -1)
+    wl.copy_(torch.randn(wl.shape, generator=torch.Generator().manual_seed(N_att)).to(DEV))
+    inf, j = float("inf"), N_att - 3
+    least = wl[:, 0].argmin(-1).tolist()
+    wl[1, :, j] = -inf
+    wl[2, G - 1, j] = inf
+    wl[3, G - 1, j] = float("nan")
+    wl[4] = float("nan")
+    wl[5, 0, :] = -inf
+    many = G > 1
+    want = [None if many else least[0], j, 0 if many else least[2], 0 if many else least[3], 0, 0]
+    B.select(p, s, pos, bufs.plan, bufs.logits, bufs.state)
+    cnt, flg, off = B.state_views(p, s, bufs.state)
+    assert cnt.tolist() == [1] * Bn and not flg.any()
+    for b in range(Bn):
+        if want[b] is not None:
+            assert int(off[b, 0]) == N_att - 1 - want[b], (b, int(off[b, 0]))
+
+
+@pytest.mark.parametrize("heads,Lp,N_att", [((4, 4), 400, 200), ((4, 4), 100, 600),
+                                            ((8, 2), 400, 200), ((8, 2), 40, 600)])
+def test_fused_split_selection_of_nan_logits(heads, Lp, N_att):
+    """The combine's selection on a window key whose logit is NaN: the same stored
+    offsets as the separate calls."""
+    Hq, Hkv = heads
+    grid, Bn, d = 32, 4, 64
+    p, s = B.make_params(Lp, grid, grid, N_att + 50, N_att), B.make_shape(Bn, Hq, Hkv, d)
+    assert B.launch_info(p, s).max_splits > 1
+    w = synth.Workload("nan", 1, Bn, Hq, Hkv, d, Lp, grid, grid, N_att + 50)
+    kv = synth.layer_kv(w, 0, DEV)
+    kv.k[1, :, Lp + 7] = float("nan")
+    kv.k[2, :, Lp + N_att - 1] = float("inf")
+    q = synth.layer_query(w, 0, DEV)
+    pos = torch.full((Bn,), N_att - 1, dtype=torch.int32, device=DEV)
+    got = []
+    for fused in (True, False):
+        bufs = B.alloc_buffers(p, s, DEV)
+        args = (p, s, q, kv.k, kv.v, B.kv_layout(kv.k), pos)
+        if fused:
+            B.decode_step(*args, bufs.state, bufs.plan, 0.1, bufs.out, bufs.logits, bufs.workspace)
+        else:
+            B.plan(p, s, pos, bufs.state, bufs.plan)
+            B.decode_attention(*args, bufs.plan, 0.1, bufs.out, bufs.logits, bufs.workspace)
+            B.select(p, s, pos, bufs.plan, bufs.logits, bufs.state)
+        got.append(B.state_views(p, s, bufs.state))
+    (cnt, flg, off), (rcnt, rflg, roff) = got
+    assert torch.equal(cnt, rcnt) and torch.equal(flg, rflg) and (cnt == 1).all()
+    assert torch.equal(off[:, 0], roff[:, 0])
+    if Hq > Hkv:
+        assert (off.view(Bn, Hkv, -1)[1, :, 0] == N_att - 1).all()  # the oldest key
