@@ -1180,14 +1180,39 @@ __device__ __forceinline__ void decode_body(const DecodeArgs& a) {
   // Merge the waves: wave w takes query heads w, w + nwaves, ... of the
   // group, and lane j columns j and j + 64.  Grouped-head workgroups of at most
   // four waves read four slots and not eight (sparse launches of more than 256
-  // workgroups 2% less on average; decode_wide_kernel, 16 slots, lost 2% of its
-  // longer calls to the second copy of the merge).
+  // workgroups 2% less on average).  One query head per KV head has no such
+  // choice, and the loops of merge_waves in place: a second copy in
+  // decode_wide_kernel, or one behind the call, cost its launches 1-2%.
   for (int g = wave; g < G; g += nwaves) {
     float M, L, A0, A1;
-    if (MF && nwaves <= 4)
-      merge_waves<4, D, G>(red, nwaves, g, lane, M, L, A0, A1);
-    else
-      merge_waves<NWM, D, G>(red, nwaves, g, lane, M, L, A0, A1);
+    if constexpr (MF) {
+      if (nwaves <= 4)
+        merge_waves<4, D, G>(red, nwaves, g, lane, M, L, A0, A1);
+      else
+        merge_waves<NWM, D, G>(red, nwaves, g, lane, M, L, A0, A1);
+    } else {
+      float mw[NWM], lw[NWM], a0[NWM], a1[NWM];
+#pragma unroll
+      for (int w = 0; w < NWM; ++w) {
+        const int wr = min(w, nwaves - 1);
+        mw[w] = red[wr][g][D];
+        lw[w] = red[wr][g][D + 1];
+        a0[w] = red[wr][g][lane];
+        a1[w] = D == 128 ? red[wr][g][(lane + 64) % D] : 0.f;
+      }
+      M = kNegBig;
+#pragma unroll
+      for (int w = 0; w < NWM; ++w) M = fmaxf(M, mw[w]);
+      L = A0 = A1 = 0.f;
+#pragma unroll
+      for (int w = 0; w < NWM; ++w) {
+        const bool ok = w < nwaves;
+        const float sw = fast_exp2(mw[w] - M);
+        L = ok ? fmaf(lw[w], sw, L) : L;
+        A0 = ok ? fmaf(a0[w], sw, A0) : A0;
+        if constexpr (D == 128) A1 = ok ? fmaf(a1[w], sw, A1) : A1;
+      }
+    }
     const int h = kvh * G + g;
     if (nsplit <= 1) {
       float inv = L > 0.f ? 1.f / L : 0.f;
