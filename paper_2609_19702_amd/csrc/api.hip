@@ -150,7 +150,7 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d) {
                                  !(pairs * S <= kOnePairs &&
                                    (tiles > kOneTilesFull || (d->D == 128 && pairs < 128))))
                           : G == 1 && (d->D == 64 || rows_max <= kOneRows ||
-                                       pairs >= kOneRowsPairs));
+                                       pairs > kOneRowsPairs));
   d->wide = one && !d->MF;
   d->wide_fp8 = false;
   if (one) {

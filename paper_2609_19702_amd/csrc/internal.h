@@ -126,10 +126,10 @@ constexpr int kKeptReadMaxWide = 256;
 // kernel costs 3.3 us of it.  On the vector-ALU tile always (32 to 256 pairs:
 // 15-30% less per layer, kept lists or not; at 512 pairs the four-wave workgroups of the general
 // kernel are 4% faster), but for few pairs of many rows of d = 128, where few
-// CUs would stream everything two tiles deep (rows over kOneRows, under
+// CUs would stream everything two tiles deep (rows over kOneRows, at most
 // kOneRowsPairs pairs: 4 pairs of 502 rows 9.1 us split and 10.8 as one
-// workgroup each, 32 pairs read by a plan 9.0 and 9.8; 432 rows 8-9% faster
-// as one).  On the MFMA tile, whose eight waves take a tile or
+// workgroup each, 32 pairs read by a plan 9.0 and 9.8, 64 pairs of 510 rows,
+// 30 of them window rows, 10.3 and 11.1; 432 rows 8-9% faster as one).  On the MFMA tile, whose eight waves take a tile or
 // two at a time, for at most kOneTilesMfma tiles of 32 rows (9 tiles, 8 pairs:
 // 10.7 -> 8.4 us) or at least kOnePairsMfma pairs (under that few CUs would
 // stream everything: 32 pairs of 15 tiles 11.0 us split, 12.2 as one) whose

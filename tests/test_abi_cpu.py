@@ -222,9 +222,9 @@ def test_binding_rejects_bad_tensors_before_the_call():
 # prompt rows, N_att[, N_r, with kept lists]) -> one split.
 ONE_WORKGROUP = [
     ((32, 1, 128, 256, 192), True),   # 448 rows
-    ((32, 1, 128, 256, 193), False),  # longer: split for fewer than 64 pairs
-    ((63, 1, 128, 12, 490), False),
-    ((64, 1, 128, 12, 490), True),
+    ((32, 1, 128, 256, 193), False),  # longer: split for at most 64 pairs
+    ((64, 1, 128, 480, 30), False),
+    ((65, 1, 128, 12, 490), True),
     ((4, 1, 64, 12, 490), True),
     # also where the launch keeps lists (skip lists of over 512 entries)
     ((72, 1, 128, 120, 115, 1152), True),

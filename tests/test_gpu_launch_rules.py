@@ -23,8 +23,8 @@ CASES = [
     ("wide_no_prompt", 12, 2, 2, 128, 0, 8, 20, 6, 0, False, 1),
     ("wide_16_tiles", 12, 3, 3, 128, 225, 12, 60, 16, 0, False, 16),
     ("wide_18_tiles", 12, 4, 4, 128, 256, 24, 256, 29, 4, False, 16),
-    ("wide_512_rows", 32, 2, 2, 128, 103, 40, 600, 409, 0, False, 16),
-    ("wide_513_rows", 32, 2, 2, 128, 104, 40, 600, 409, 0, True, 4),
+    ("wide_512_rows", 33, 2, 2, 128, 103, 40, 600, 409, 0, False, 16),
+    ("wide_513_rows", 33, 2, 2, 128, 104, 40, 600, 409, 0, True, 4),
     ("few_448_rows", 8, 2, 2, 128, 70, 40, 600, 378, 4, False, 16),
     ("few_449_rows", 8, 2, 2, 128, 71, 40, 600, 378, 4, True, 2),
     ("wide_d64", 12, 5, 5, 64, 121, 20, 130, 41, 4, False, 6),
