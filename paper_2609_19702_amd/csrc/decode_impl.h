@@ -1358,7 +1358,7 @@ __device__ __forceinline__ void combine_one(const DecodeArgs& a, int lane, int b
     x0[j] = j < nsplit ? p.x0[j] : 0.f;
     x1[j] = j < nsplit ? p.x1[j] : 0.f;
   }
-  for (int j0 = 0; j0 < nsplit; j0 += kA) {
+  auto add = [&](int j0, const float (&r0)[kA], const float (&r1)[kA]) {
     if (j0 > 0 && j0 % 64 == 0) {  // weights of the next 64 splits
       const int sl = j0 + lane;
       w = sl < nsplit ? fast_exp2(pp[sl * sstride + D] - M) : 0.f;
@@ -1366,15 +1366,18 @@ __device__ __forceinline__ void combine_one(const DecodeArgs& a, int lane, int b
 #pragma unroll
     for (int j = 0; j < kA; ++j) {
       const float sw = j0 + j < nsplit ? __shfl(w, (j0 + j) & 63, 64) : 0.f;
-      A0 = fmaf(x0[j], sw, A0);
-      if constexpr (D == 128) A1 = fmaf(x1[j], sw, A1);
+      A0 = fmaf(r0[j], sw, A0);
+      if constexpr (D == 128) A1 = fmaf(r1[j], sw, A1);
     }
-#pragma unroll
-    for (int j = 0; j < kA; ++j) {
-      x0[j] = y0[j];
-      x1[j] = y1[j];
-    }
-    if (j0 + 2 * kA < nsplit) load_rows(j0 + 2 * kA, y0, y1);
+  };
+  // Two sets of rows in turn, each loaded again as soon as it is added (copied
+  // from one to the other, a wait for the second preceded every load).
+  for (int j0 = 0; j0 < nsplit; j0 += 2 * kA) {
+    add(j0, x0, x1);
+    if (j0 + 2 * kA < nsplit) load_rows(j0 + 2 * kA, x0, x1);
+    if (j0 + kA >= nsplit) break;
+    add(j0 + kA, y0, y1);
+    if (j0 + 3 * kA < nsplit) load_rows(j0 + 3 * kA, y0, y1);
   }
   float inv = L > 0.f ? 1.f / L : 0.f;
   if (a.vs) inv *= a.vs[pair_of(a, b, kvh)];
