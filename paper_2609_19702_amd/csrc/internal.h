@@ -59,8 +59,8 @@ dsa_status derive(const dsa_params* p, const dsa_shape* s, Derived* d);
 #define DSA_TUNE_MIN_WGS 512  // split further while a launch has fewer workgroups (dense mode)
 #endif
 #ifndef DSA_TUNE_MIN_WGS_SPARSE
-#define DSA_TUNE_MIN_WGS_SPARSE 256  // the same in the sparse modes (fewer, larger splits of
-#endif                               // single requests: 0.3-1 us per layer less at batch 1)
+#define DSA_TUNE_MIN_WGS_SPARSE 256  // the same in the sparse modes, for launches that do not
+#endif                               // take one workgroup per pair (kOnePairs)
 #ifndef DSA_TUNE_MAX_FUSED_SPLIT
 #define DSA_TUNE_MAX_FUSED_SPLIT 512  // most rows of a sparse-mode split (the fused step keeps
                                       // their logits and positions in LDS), vector-ALU tile
