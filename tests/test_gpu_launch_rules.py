@@ -12,7 +12,7 @@ from oracle import step as ostep
 from paper_2609_19702_amd import binding as B
 from paper_2609_19702_amd import synth
 from tests.gpu_util import (DEV, c_replay_states, check_layer_vs_oracle, fp8_request_arrays,
-                            request_arrays, say, states_to_buffer)
+                            launches, request_arrays, say, states_to_buffer)
 from tests.test_gpu_mfma_tiles import positions, run
 
 pytestmark = pytest.mark.gpu
@@ -197,6 +197,36 @@ def test_long_skip_plans_from_dense_to_sparse_windows(N_r, N_att, grid):
     for pair in range(2 * len(ts)):
         want = [int(x) for x in kept[pair // 2][pair % 2]]
         assert idx[pair, :int(cnt[pair])].tolist() == want, (ts[pair // 2], pair % 2)
+
+
+def test_long_skip_plans_across_the_pair_rules():
+    """The same requests planned 16, 528 (no loads ahead of the position) and 2064
+    at a time (a wave per pair again for 1110 entries): the same plans."""
+    N_r, N_att, grid = 1200, 90, 40
+    ts = [-1, 0, 1, 88, 89, 90, 130, 640, 1198, 1199, 1200, 1599, 5000, 700, 900, 1100]
+    p = B.make_params(8, grid, grid, N_r, N_att)
+    states, _ = c_replay_states(N_r, N_att, grid * grid, [min(t, 1599) for t in ts], 1,
+                                random.Random(3))
+    ref, kernels = None, set()
+    for times in (1, 33, 129):
+        n = 16 * times
+        s = B.make_shape(n, 1, 1, 64)
+        one = states_to_buffer(p, B.make_shape(16, 1, 1, 64), states, [min(t, 1599) for t in ts])
+        st = torch.zeros(B.state_bytes(p, s), dtype=torch.uint8, device=DEV)
+        for dst, src in zip(B.state_views(p, s, st), B.state_views(p, B.make_shape(16, 1, 1, 64), one)):
+            dst.copy_(src.repeat(*([times] + [1] * (src.dim() - 1))))
+        pos = torch.tensor(ts * times, dtype=torch.int32, device=DEV)
+        buf = torch.zeros(B.plan_bytes(p, s), dtype=torch.uint8, device=DEV)
+        (got,) = launches(lambda: B.plan(p, s, pos, st, buf))
+        kernels.add(got[3])
+        torch.cuda.synchronize()
+        views = [v.view(times, 16, *v.shape[1:]) for v in B.plan_views(p, s, buf)]
+        if ref is None:
+            ref = [v[0] for v in views]
+            assert ref[0].tolist() == [0 if t < 0 else min(t + 1, N_att) for t in ts]
+        for v, r in zip(views, ref):
+            assert (v == r).all()
+    assert len(kernels) == 3
 
 
 @pytest.mark.parametrize("d,heads,most", [(64, (2, 2), 73), (128, (4, 2), 42)])
